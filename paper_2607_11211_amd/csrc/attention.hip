@@ -70,12 +70,13 @@ constexpr int kMaxSplits = 256;   // splits per (sequence, kv head); one combine
 constexpr int kXchMinTiles = 8;
 
 // one (split, KV head, sequence) per block
-template <int D, int G, int NRING, bool PBF16, int KVF, bool XCH>
+template <int D, int G, int NRING, bool PBF16, int KVF, bool XCH, bool PARTS>
 __device__ __forceinline__ void attn_split_body(const AttnArgs& a, float kscale, float vscale) {
-  using Body = attn::AttnBody<D, G, NRING, PBF16, KVF, attn::GlobalIO, XCH>;
+  using IO = attn::GlobalIO<PARTS>;
+  using Body = attn::AttnBody<D, G, NRING, PBF16, KVF, IO, XCH>;
   __shared__ attn::AttnSmem<D, G, KVF> sm;
   __shared__ v4u xch[XCH ? 2 * (kThreads / kWave) * Body::SPAN : 1];  // K spans, then V spans
-  Body body(a, attn::GlobalIO{}, sm, threadIdx.x, blockIdx.x, blockIdx.y, a.order.p[blockIdx.z], true, xch,
+  Body body(a, IO{}, sm, threadIdx.x, blockIdx.x, blockIdx.y, a.order.p[blockIdx.z], true, xch,
             xch + (kThreads / kWave) * Body::SPAN);
   body.load_prologue();
   __builtin_amdgcn_sched_barrier(0);  // keep the prologue loads ahead of the tiles
@@ -86,17 +87,17 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a, float kscale,
 // At least two waves per SIMD: the groups of four at d = 128 (one tile in
 // flight per lane, o of four heads in registers) then fit 256 registers
 // without spilling, so two blocks share a CU instead of one.
-template <int D, int G, int NRING, bool PBF16, bool XCH>
+template <int D, int G, int NRING, bool PBF16, bool XCH, bool PARTS>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void attn_split_kernel(AttnArgs a) {
-  attn_split_body<D, G, NRING, PBF16, kKvBf16, XCH>(a, 1.f, 1.f);
+  attn_split_body<D, G, NRING, PBF16, kKvBf16, XCH, PARTS>(a, 1.f, 1.f);
 }
 
 // 8-bit cache: the KV head's two scales come from the argument block; tiles
 // in flight as for a bf16 cache
-template <int D, int G, int KVF>
+template <int D, int G, int KVF, bool PARTS>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void attn_split_kv8_kernel(
     AttnArgs a, KvScales sc) {
-  attn_split_body<D, G, (G <= 2 ? 2 : 1), false, KVF, false>(a, sc.k[blockIdx.y], sc.v[blockIdx.y]);
+  attn_split_body<D, G, (G <= 2 ? 2 : 1), false, KVF, false, PARTS>(a, sc.k[blockIdx.y], sc.v[blockIdx.y]);
 }
 
 // o[b, h] = sum_s e^{m_s - M} o_s / sum_s e^{m_s - M} l_s,  M = max_s m_s.
@@ -111,11 +112,24 @@ constexpr int kCombineThreads = 1024;
 constexpr int kCombineRegs = 32;  // splits per thread held in registers
 static_assert(kCombineThreads / 128 * kCombineRegs >= kMaxSplits, "one round of loads covers every split");
 
+// o at input k of sequence b for the MFMA O projection: its hi/lo bf16 split
+// in the lane order of the A operand (up to 16 sequences: row 2 (b % 8) +
+// level, k-group (k / 8) % 4 of k-tile k / 32, batch tile b / 8)
+__device__ __forceinline__ void put_o_operand(uint16_t* op, int nbtc, int wide, int b, int k, float v) {
+  const uint16_t hi = f32_to_bf16(v);
+  const uint16_t lo = f32_to_bf16(v - bf16_to_f32(hi));
+  const size_t at = wide ? wide_operand_offset(b, k, nbtc)
+                         : (((size_t)(k >> 5) * nbtc + b / 8) * kWave + 2 * (b % 8) + 16 * ((k >> 3) & 3)) * 8 + (k & 7);
+  op[at] = hi;
+  op[at + (wide ? kWave * 8 : 8)] = lo;
+}
+
 template <int D>
 __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(const float* __restrict__ part, int nsplit,
                                                                        int nsplit_cap, int n_heads,
                                                                        float* __restrict__ o,
-                                                                       uint16_t* __restrict__ o_operand, int o_nbtc) {
+                                                                       uint16_t* __restrict__ o_operand, int o_nbtc,
+                                                                       int o_wide) {
   constexpr int NG = kCombineThreads / D;  // thread groups over the splits
   __shared__ float fac[kMaxSplits];
   __shared__ float red[kCombineThreads / kWave];
@@ -157,18 +171,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(const flo
     for (int g2 = 0; g2 < NG; ++g2) O += osum[g2][tid];
     const float ov2 = O / L;
     o[((size_t)b * n_heads + h) * D + tid] = ov2;
-    if (o_operand) {
-      // the MFMA O projection's operand: hi/lo bf16 split of o at input
-      // k = h D + tid, in the lane order of the A operand (row 2 (b % 8) +
-      // level, k-group (k / 8) % 4 of k-tile k / 32, batch tile b / 8)
-      const int k = h * D + tid;
-      const uint16_t hi = f32_to_bf16(ov2);
-      const uint16_t lo = f32_to_bf16(ov2 - bf16_to_f32(hi));
-      const size_t base = (((size_t)(k >> 5) * o_nbtc + b / 8) * kWave + 2 * (b % 8) + 16 * ((k >> 3) & 3)) * 8 +
-                          (k & 7);
-      o_operand[base] = hi;
-      o_operand[base + 8] = lo;
-    }
+    if (o_operand) put_o_operand(o_operand, o_nbtc, o_wide, b, h * D + tid, ov2);
   }
 }
 
@@ -184,7 +187,8 @@ constexpr int kWaveCombineSplits = 32;
 template <int D, int NS>
 __global__ __launch_bounds__(kWave) void attn_combine_wave_kernel(const float* __restrict__ part, int nsplit,
                                                                  int nsplit_cap, int n_heads, float* __restrict__ o,
-                                                                 uint16_t* __restrict__ o_operand, int o_nbtc) {
+                                                                 uint16_t* __restrict__ o_operand, int o_nbtc,
+                                                                       int o_wide) {
   constexpr int EPL = (D + kWave - 1) / kWave;  // o elements per lane
   const int lane = threadIdx.x;
   const int h = blockIdx.x, b = blockIdx.y;
@@ -217,21 +221,12 @@ __global__ __launch_bounds__(kWave) void attn_combine_wave_kernel(const float* _
     if (e < D) {
       const float v = acc[i] / L;
       o[((size_t)b * n_heads + h) * D + e] = v;
-      if (o_operand) {
-        // the MFMA O projection's operand, as in attn_combine_kernel
-        const int k = h * D + e;
-        const uint16_t hi = f32_to_bf16(v);
-        const uint16_t lo = f32_to_bf16(v - bf16_to_f32(hi));
-        const size_t base = (((size_t)(k >> 5) * o_nbtc + b / 8) * kWave + 2 * (b % 8) + 16 * ((k >> 3) & 3)) * 8 +
-                            (k & 7);
-        o_operand[base] = hi;
-        o_operand[base + 8] = lo;
-      }
+      if (o_operand) put_o_operand(o_operand, o_nbtc, o_wide, b, h * D + e, v);
     }
   }
 }
 
-template <int D, int G>
+template <int D, int G, bool PARTS>
 hipError_t launch_dg(const AttnArgs& a, hipStream_t s, KernelEvents ev) {
   // tiles in flight per lane: a tile is D / 8 registers of K and V; the
   // query quarter and the softmax state take (D / 4 + 2) G more. Two for one
@@ -249,19 +244,19 @@ hipError_t launch_dg(const AttnArgs& a, hipStream_t s, KernelEvents ev) {
   const int tiles = (maxp + attn::kTile - 1) / attn::kTile;
   if constexpr (G <= 2) {
     if ((tiles + a.nsplit - 1) / a.nsplit >= kXchMinTiles)
-      return a.p_bf16 ? ext_launch(attn_split_kernel<D, G, NRING, true, true>, grid, dim3(kThreads), 0, s, ev, a)
-                      : ext_launch(attn_split_kernel<D, G, NRING, false, true>, grid, dim3(kThreads), 0, s, ev, a);
+      return a.p_bf16 ? ext_launch(attn_split_kernel<D, G, NRING, true, true, PARTS>, grid, dim3(kThreads), 0, s, ev, a)
+                      : ext_launch(attn_split_kernel<D, G, NRING, false, true, PARTS>, grid, dim3(kThreads), 0, s, ev, a);
   }
-  return a.p_bf16 ? ext_launch(attn_split_kernel<D, G, NRING, true, false>, grid, dim3(kThreads), 0, s, ev, a)
-                  : ext_launch(attn_split_kernel<D, G, NRING, false, false>, grid, dim3(kThreads), 0, s, ev, a);
+  return a.p_bf16 ? ext_launch(attn_split_kernel<D, G, NRING, true, false, PARTS>, grid, dim3(kThreads), 0, s, ev, a)
+                  : ext_launch(attn_split_kernel<D, G, NRING, false, false, PARTS>, grid, dim3(kThreads), 0, s, ev, a);
 }
 
-template <int D, int G>
+template <int D, int G, bool PARTS>
 hipError_t launch_kv8_dg(const AttnArgs& a, const KvScales& sc, hipStream_t s, KernelEvents ev) {
   dim3 grid(a.nsplit, a.n_kv_heads, a.batch);
   switch (a.kv_format) {
-    case kKvFp8: return ext_launch(attn_split_kv8_kernel<D, G, kKvFp8>, grid, dim3(kThreads), 0, s, ev, a, sc);
-    case kKvInt8: return ext_launch(attn_split_kv8_kernel<D, G, kKvInt8>, grid, dim3(kThreads), 0, s, ev, a, sc);
+    case kKvFp8: return ext_launch(attn_split_kv8_kernel<D, G, kKvFp8, PARTS>, grid, dim3(kThreads), 0, s, ev, a, sc);
+    case kKvInt8: return ext_launch(attn_split_kv8_kernel<D, G, kKvInt8, PARTS>, grid, dim3(kThreads), 0, s, ev, a, sc);
     default: return hipErrorInvalidValue;
   }
 }
@@ -269,9 +264,9 @@ hipError_t launch_kv8_dg(const AttnArgs& a, const KvScales& sc, hipStream_t s, K
 template <int D>
 hipError_t launch_kv8_d(const AttnArgs& a, const KvScales& sc, hipStream_t s, KernelEvents ev) {
   switch (a.n_heads / a.n_kv_heads) {
-    case 1: return launch_kv8_dg<D, 1>(a, sc, s, ev);
-    case 2: return launch_kv8_dg<D, 2>(a, sc, s, ev);
-    case 4: return launch_kv8_dg<D, 4>(a, sc, s, ev);
+    case 1: return a.qkv_part ? launch_kv8_dg<D, 1, true>(a, sc, s, ev) : launch_kv8_dg<D, 1, false>(a, sc, s, ev);
+    case 2: return a.qkv_part ? launch_kv8_dg<D, 2, true>(a, sc, s, ev) : launch_kv8_dg<D, 2, false>(a, sc, s, ev);
+    case 4: return a.qkv_part ? launch_kv8_dg<D, 4, true>(a, sc, s, ev) : launch_kv8_dg<D, 4, false>(a, sc, s, ev);
     default: return hipErrorInvalidValue;
   }
 }
@@ -279,9 +274,9 @@ hipError_t launch_kv8_d(const AttnArgs& a, const KvScales& sc, hipStream_t s, Ke
 template <int D>
 hipError_t launch_d(const AttnArgs& a, hipStream_t s, KernelEvents ev) {
   switch (a.n_heads / a.n_kv_heads) {
-    case 1: return launch_dg<D, 1>(a, s, ev);
-    case 2: return launch_dg<D, 2>(a, s, ev);
-    case 4: return launch_dg<D, 4>(a, s, ev);
+    case 1: return a.qkv_part ? launch_dg<D, 1, true>(a, s, ev) : launch_dg<D, 1, false>(a, s, ev);
+    case 2: return a.qkv_part ? launch_dg<D, 2, true>(a, s, ev) : launch_dg<D, 2, false>(a, s, ev);
+    case 4: return a.qkv_part ? launch_dg<D, 4, true>(a, s, ev) : launch_dg<D, 4, false>(a, s, ev);
     default: return hipErrorInvalidValue;
   }
 }
@@ -291,12 +286,12 @@ hipError_t launch_combine_d(const AttnArgs& a, hipStream_t s, KernelEvents ev) {
   dim3 grid(a.n_heads, a.batch);
   if (a.nsplit <= kWaveCombineSplits / 2)
     return ext_launch(attn_combine_wave_kernel<D, kWaveCombineSplits / 2>, grid, dim3(kWave), 0, s, ev,
-                      (const float*)a.part, a.nsplit, a.nsplit_cap, a.n_heads, a.o, a.o_operand, a.o_nbtc);
+                      (const float*)a.part, a.nsplit, a.nsplit_cap, a.n_heads, a.o, a.o_operand, a.o_nbtc, a.o_wide);
   if (a.nsplit <= kWaveCombineSplits)
     return ext_launch(attn_combine_wave_kernel<D, kWaveCombineSplits>, grid, dim3(kWave), 0, s, ev,
-                      (const float*)a.part, a.nsplit, a.nsplit_cap, a.n_heads, a.o, a.o_operand, a.o_nbtc);
+                      (const float*)a.part, a.nsplit, a.nsplit_cap, a.n_heads, a.o, a.o_operand, a.o_nbtc, a.o_wide);
   return ext_launch(attn_combine_kernel<D>, grid, dim3(kCombineThreads), 0, s, ev, (const float*)a.part, a.nsplit,
-                    a.nsplit_cap, a.n_heads, a.o, a.o_operand, a.o_nbtc);
+                    a.nsplit_cap, a.n_heads, a.o, a.o_operand, a.o_nbtc, a.o_wide);
 }
 
 }  // namespace

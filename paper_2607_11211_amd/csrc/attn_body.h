@@ -174,8 +174,13 @@ __device__ __forceinline__ void tile_load_contig(v4u (&k)[NC], v4u (&v)[NC], con
 
 // Plain global-memory IO of the attention kernel. rec() is where the split's
 // record (m, l, -, -, o) of query head `head` of sequence b goes.
+// PARTS: q|k|v come in two parts (large batches). A template flag, so that the
+// count of loads ahead of the ring is known.
+template <bool PARTS = false>
 struct GlobalIO {
-  __device__ __forceinline__ float qkv(const AttnArgs& a, size_t i) const { return a.qkv[i]; }
+  __device__ __forceinline__ float qkv(const AttnArgs& a, size_t i) const {
+    return PARTS ? a.qkv[i] + a.qkv[i + a.qkv_part] : a.qkv[i];
+  }
   __device__ __forceinline__ void part(float* p, float v) const { *p = v; }
   __device__ __forceinline__ float* rec(const AttnArgs& a, int b, int head, int s, int D) const {
     return a.part + (((size_t)b * a.n_heads + head) * a.nsplit_cap + s) * (D + kPartLead);
@@ -432,7 +437,7 @@ struct AttnBody {
       if (tid < HALF) {
         // k and its cos/sin row again from memory (not held across the loop)
         const size_t kg = (size_t)b * (H + 2 * Hkv) * D + (size_t)H * D + (size_t)g * D;
-        const double kk0 = a.qkv[kg + pj], kk1 = a.qkv[kg + pj + HALF];
+        const double kk0 = io.qkv(a, kg + pj), kk1 = io.qkv(a, kg + pj + HALF);
         const double c = a.rope_cos[(size_t)P * HALF + pj], sn = a.rope_sin[(size_t)P * HALF + pj];
         float* dk = dq + (size_t)H * D + (size_t)g * D;
         dk[pj] = (float)(kk0 * c - kk1 * sn);

@@ -83,6 +83,13 @@ __device__ __forceinline__ uint16_t f64_to_bf16(double x) {
   return f32_to_bf16(__uint_as_float(u));
 }
 
+// Element offset of the hi level of input k of sequence b in an operand of the
+// large-batch MFMA projections: [k-tile][16-sequence tile][level][lane][8],
+// nbtc / 2 sequence tiles; the lo level is kWave * 8 elements further on.
+__device__ __forceinline__ size_t wide_operand_offset(int b, int k, int nbtc) {
+  return (((size_t)(k >> 5) * nbtc + 2 * (b / 16)) * kWave + b % 16 + 16 * ((k >> 3) & 3)) * 8 + (k & 7);
+}
+
 // Eight bf16 (one 16-byte load) dotted with eight floats.
 __device__ __forceinline__ float dot8(const uint4 w, const float* h) {
   float s = bf16_lo(w.x) * h[0];

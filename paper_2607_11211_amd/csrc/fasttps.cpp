@@ -116,6 +116,21 @@ constexpr int kMfmaWaves = 16;  // waves per block of the MFMA kernels (they spl
 // intermediate unit is one contiguous 2D-value row for the projection kernel.
 constexpr int kInterlaceTile = 1;
 
+// Beyond 16 sequences the kernels of mfma_proj.hip stream the weights once per
+// 16 sequences, those of mfma_wide.hip once, at three launches more (the QKV
+// operand and two sums of parts, about 9 us). The line lies where what is
+// read again costs as much: on MI355X, layer steps at 64 cached entries,
+// mfma_proj against mfma_wide: hidden 512 (6 MB a layer) at 64 sequences 36.3
+// against 39.6 us, hidden 1024 (26 MB) 36.6 against 37.6 us at 32 and 49.4
+// against 41.6 at 33, Phi-3 (227 MB) 122.3 against 82.8 us at 32 and 233.5
+// against 109.1 at 64.
+constexpr size_t kWideMinReread = size_t(32) << 20;
+bool wide_pays(const fasttps_config& c, int batch) {
+  const size_t D = c.hidden, q = (size_t)c.n_heads * c.head_dim, kv = (size_t)c.n_kv_heads * c.head_dim;
+  const size_t weight_bytes = 2 * (D * (q + 2 * kv) + D * q + 3 * D * c.intermediate);
+  return batch >= kWideMinBatch && weight_bytes * ((batch - 1) / 16) >= kWideMinReread;
+}
+
 // test-hook buffers a step wrote (fasttps_layer::dbg_written)
 constexpr int kDbgQk = 1, kDbgNorm = 2;
 
@@ -195,6 +210,7 @@ struct fasttps_layer {
   int mlp_path = FASTTPS_MLP_SPLIT;
   int weight_layout = FASTTPS_WEIGHTS_ROWS_AND_TILES;  // how later packs store the projections
   float* mlp_part = nullptr;
+  size_t qkv_part = 0;         // the last step's q|k|v came in two parts this far apart (else 0)
   bool mlp_a_written = false;  // the last step stored h^sm (FASTTPS_DBG_MLP_A)
   // the fused kernel's phase hand-over: per-block phase flags, the epoch of
   // the last completed launch, the count of bounded waits that ran out
@@ -350,15 +366,18 @@ int fasttps_layer_create(const fasttps_config* cfg, fasttps_layer** out) {
     const TileDims* tds[3] = {&lt.o, &lt.gu, &lt.down};
     for (int i = 0; i < 3; ++i) {
       size_t f = 0, t = 0;
-      mfma_split_need(i + 1, tds[i]->ns, tds[i]->kt, tds[i]->rh, B, &f, &t);
+      mfma_split_need(i + 1, tds[i]->ns, tds[i]->kt, tds[i]->rh, std::min(B, kWideMinBatch - 1), &f, &t);
       split_floats = std::max(split_floats, f);
       split_tickets = std::max(split_tickets, t);
+      if (i != 1)
+        split_floats = std::max(split_floats,
+                                wide_part_floats(tds[i]->ns, tds[i]->kt, tds[i]->rh, c.hidden, B));
     }
   }
   size_t sizes[17] = {
       cs.size() * sizeof(double),
       sn.size() * sizeof(double),
-      (size_t)B * qkv_rows * sizeof(float),
+      (size_t)B * qkv_rows * sizeof(float) * (B >= kWideMinBatch ? kWideQkvParts : 1),
       (size_t)B * c.n_heads * nsplit_cap * (d + kPartLead) * sizeof(float),
       (size_t)B * c.n_heads * d * sizeof(float),
       (size_t)B * c.hidden * sizeof(float),
@@ -418,7 +437,7 @@ int fasttps_layer_create(const fasttps_config* cfg, fasttps_layer** out) {
     l->op_down = reinterpret_cast<uint16_t*>(base + offs[9]);
     l->ssq_h1 = reinterpret_cast<float*>(base + offs[10]);
     l->nbtc = nbtc;
-    if (split_floats && split_tickets) {
+    if (split_floats) {
       l->split_part = reinterpret_cast<float*>(base + offs[15]);
       l->split_tickets = reinterpret_cast<unsigned*>(base + offs[16]);
       l->split_part_cap = split_floats;
@@ -784,6 +803,8 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
   if (mfma && !have_tiles)
     return fail(FASTTPS_ERR_INVALID_ARG, "the matrix-core path needs a layer and weights with max_batch > 1");
 
+  const bool wide = mfma && wide_pays(c, batch);
+
   const int nsplit = attention_splits(l, pos, batch, maxp);
 
   // one sequence: the whole step as one persistent kernel, on request
@@ -867,6 +888,7 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
 
   AttnArgs aa{};
   aa.qkv = S.qkv;
+  aa.qkv_part = wide ? (size_t)batch * qa.rows : 0;
   aa.rope_cos = l->rope_cos;
   aa.rope_sin = l->rope_sin;
   aa.k_cache = static_cast<uint16_t*>(k_cache);
@@ -875,6 +897,7 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
   aa.o = S.o;
   aa.o_operand = mfma ? l->op_o : nullptr;
   aa.o_nbtc = l->nbtc;
+  aa.o_wide = wide;
   aa.batch = batch;
   aa.n_heads = c.n_heads;
   aa.n_kv_heads = c.n_kv_heads;
@@ -893,6 +916,7 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
 
   if (!S.noalloc) {
     l->dbg_written = 0;
+    l->qkv_part = aa.qkv_part;
     l->mlp_a_written = !mlp_fused;  // h^sm is stored by every path but the fused MLP
   }
   if (fused) {
@@ -942,7 +966,13 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
     m.x_bf16 = xb;
     m.gamma = w->attn_norm;
     m.out = S.qkv;
-    if ((e = launch_mfma_qkv(m, s, ev[0])) != hipSuccess) return hip_fail(e, "qkv launch");
+    if (wide) {
+      // the QKV operand and 1/rms(x) in buffers the O projection fills later
+      // (the gate/up operand has the same inputs)
+      if ((e = launch_wide_qkv(m, l->op_gu, l->ssq_h1, s, ev[0])) != hipSuccess) return hip_fail(e, "qkv launch");
+    } else if ((e = launch_mfma_qkv(m, s, ev[0])) != hipSuccess) {
+      return hip_fail(e, "qkv launch");
+    }
   } else {
     if ((e = launch_rmsnorm_qkv(qa, s, ev[0])) != hipSuccess) return hip_fail(e, "qkv launch");
   }
@@ -969,19 +999,23 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
     m.out = S.h1;
     m.a_out = l->op_gu;
     m.ssq_out = l->ssq_h1;
-    if ((e = launch_mfma_oproj(m, s, ev[3])) != hipSuccess) return hip_fail(e, "o-proj launch");
+    e = wide ? launch_wide_oproj(m, l->ssq_h1, s, ev[3]) : launch_mfma_oproj(m, s, ev[3]);
+    if (e != hipSuccess) return hip_fail(e, "o-proj launch");
     m = mfma_args(lt.gu, w->t_gu, c.intermediate, (int)D);
     m.a_in = l->op_gu;
     m.ssq_in = l->ssq_h1;
     m.ns_in = lt.o.ns;
     m.out = S.a;
     m.a_out = l->op_down;
-    if ((e = launch_mfma_gate_up(m, s, ev[4])) != hipSuccess) return hip_fail(e, "mlp gate/up launch");
+    m.inv_in = l->ssq_h1;
+    e = wide ? launch_wide_gate_up(m, s, ev[4]) : launch_mfma_gate_up(m, s, ev[4]);
+    if (e != hipSuccess) return hip_fail(e, "mlp gate/up launch");
     m = mfma_args(lt.down, w->t_down, (int)D, c.intermediate);
     m.a_in = l->op_down;
     m.res_f32 = S.h1;
     m.out_bf16 = static_cast<uint16_t*>(y);
-    if ((e = launch_mfma_down(m, s, ev[5])) != hipSuccess) return hip_fail(e, "mlp down launch");
+    e = wide ? launch_wide_down(m, s, ev[5]) : launch_mfma_down(m, s, ev[5]);
+    if (e != hipSuccess) return hip_fail(e, "mlp down launch");
   } else {
     if (merge_in_o) {
       MergeArgs ma{};
@@ -1109,6 +1143,12 @@ int fasttps_debug_read(fasttps_layer* l, int32_t which, int32_t batch, void* dst
   }
   n *= (size_t)batch * sizeof(float);
   if (bytes != n) return fail(FASTTPS_ERR_INVALID_ARG, "bytes %zu != %zu", bytes, n);
+  if (which == FASTTPS_DBG_QKV && l->qkv_part) {
+    const hipError_t e = launch_wide_qkv_sum(l->qkv, l->qkv_part, n / sizeof(float), static_cast<float*>(dst),
+                                             static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return hip_fail(e, "debug copy");
+    return FASTTPS_OK;
+  }
   hipError_t e = hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToDevice, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "debug copy");
   return FASTTPS_OK;

@@ -119,6 +119,9 @@ struct MfmaArgs {
   unsigned* tickets;
   size_t kpart_cap, tickets_cap;
   int ks, ktq, kstride;     // set by the launcher: parts, k-tiles per part, floats per block of kpart
+  // large batches (mfma_wide.hip)
+  const float* inv_in;      // QKV, gate/up: 1/rms per sequence
+  int passes;               // set by the launcher
 };
 // the split scratch a projection needs at up to `batch` sequences (mode 0
 // QKV, 1 O, 2 gate/up, 3 down; ns stripes of rh rows and kt k-tiles)
@@ -127,6 +130,21 @@ hipError_t launch_mfma_qkv(const MfmaArgs& a, hipStream_t s, KernelEvents ev = {
 hipError_t launch_mfma_oproj(const MfmaArgs& a, hipStream_t s, KernelEvents ev = {});
 hipError_t launch_mfma_gate_up(const MfmaArgs& a, hipStream_t s, KernelEvents ev = {});
 hipError_t launch_mfma_down(const MfmaArgs& a, hipStream_t s, KernelEvents ev = {});
+// The same projections for large batches (mfma_wide.hip), their operands in
+// the layout of wide_operand_offset.
+constexpr int kWideMinBatch = 17;
+constexpr int kWideMaxParts = 4;  // parts of the O and down projections
+constexpr int kWideQkvParts = 2;  // parts of q|k|v: out is [kWideQkvParts][batch][rows]
+// floats of kpart the O or down projection needs for up to `batch` sequences
+size_t wide_part_floats(int ns, int kt, int rh, int rows, int batch);
+// op, inv: room for the QKV operand and 1/rms(x)
+hipError_t launch_wide_qkv(const MfmaArgs& a, uint16_t* op, float* inv, hipStream_t s, KernelEvents ev = {});
+// inv: RMSNorm2's factor per sequence
+hipError_t launch_wide_oproj(const MfmaArgs& a, float* inv, hipStream_t s, KernelEvents ev = {});
+hipError_t launch_wide_gate_up(const MfmaArgs& a, hipStream_t s, KernelEvents ev = {});
+hipError_t launch_wide_down(const MfmaArgs& a, hipStream_t s, KernelEvents ev = {});
+// dst[n] = the two parts of q|k|v, `part` floats apart, added
+hipError_t launch_wide_qkv_sum(const float* parts, size_t part, size_t n, float* dst, hipStream_t s);
 // the MFMA-tiled copy of a row-major [rows, din] matrix with row stride ld,
 // in stripes of rh rows; with `up` set, stripes of rh / 2 rows of src (gate)
 // and the rh / 2 matching rows of up
@@ -139,6 +157,7 @@ constexpr int kPartLead = 4;
 
 struct AttnArgs {
   const float* qkv;        // [batch, (H + 2 H_kv) d] fp32, before RoPE
+  size_t qkv_part;         // large batches: floats from q|k|v to its second part, to be added (else 0)
   const double* rope_cos;  // [N_max, d/2]
   const double* rope_sin;  // [N_max, d/2]
   void* k_cache;           // [B, H_kv, N_max, d], bf16 or 8-bit codes
@@ -147,6 +166,7 @@ struct AttnArgs {
   float* o;                // [batch, H d] fp32
   uint16_t* o_operand;     // if set: o split for the MFMA O projection [kt][o_nbtc][64][8]
   int o_nbtc;
+  int o_wide;              // its layout: that of wide_operand_offset (large batches)
   int batch, n_heads, n_kv_heads, head_dim, max_seq;
   int nsplit, nsplit_cap;     // splits per (sequence, KV head): split s takes tiles s, s + nsplit, ...
   float scale;             // 1/sqrt(d)

@@ -1,0 +1,117 @@
+"""The projections of large batches (17 to 64 sequences, mfma_wide.hip)
+against the fp64 oracle, through the C ABI (MI355X), to the bars of the other
+projection paths: sequence tiles of 16 filled and ragged, one stripe per block
+up to several passes of stripes, k-tiles fewer than the block's waves, padded
+stripes and k-tiles, parts, and steps below and above the 16-sequence
+limit on one handle."""
+import numpy as np
+import pytest
+
+from gpu_harness import full_check, log, run_gpu
+from oracle import ref
+from paper_2607_11211_amd import inputs
+from paper_2607_11211_amd.configs import LayerConfig
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2607_11211_amd.layer  # noqa: F401  (fails loudly if the library is missing)
+
+
+def _cfg(name, index, batch, hidden, heads, kv, d, inter, max_seq=40):
+    return LayerConfig(name=name, index=index, batch=batch, hidden=hidden, n_heads=heads, n_kv_heads=kv, head_dim=d,
+                       intermediate=inter, rope_base=10000.0, max_seq=max_seq,
+                       pos=tuple((7 * i + 3) % max_seq for i in range(batch)))
+
+
+# sizes past the line of the dispatch (32 MB of weights read again by the kernels of 16 sequences)
+SHAPES = [
+    # one sequence past the limit; hidden 776 pads stripes and k-tiles
+    _cfg("w_b17", 100, 17, 776, 8, 8, 96, 6408, 130),
+    # two full sequence tiles; QKV in 12 stripes per block (two passes of 6), gate/up in two of 5;
+    # hidden 192: six k-tiles for eight waves
+    _cfg("w_b32_rows", 101, 32, 192, 64, 64, 128, 20000),
+    # the same with four sequence tiles and two k-tiles
+    _cfg("w_b64_rows", 102, 64, 64, 64, 64, 128, 20000),
+    # three tiles, the last of one sequence; groups of four
+    _cfg("w_b33", 103, 33, 512, 8, 2, 64, 5224, 70),
+    # O and down projections in 4 parts (4096 and 4192 inputs), 49 and 20 sequences
+    _cfg("w_parts_b49", 104, 49, 256, 32, 8, 128, 4192),
+    _cfg("w_parts_b20", 105, 20, 264, 32, 8, 128, 17408),
+    # wide inputs against few units
+    _cfg("w_din_b48", 106, 48, 4096, 4, 4, 64, 384),
+    # the widest MLP: 1024 k-tiles in the down projection
+    _cfg("w_longk_b18", 107, 18, 168, 1, 1, 128, 32768),
+]
+
+
+@pytest.mark.parametrize("cfg", SHAPES, ids=lambda c: c.name)
+def test_wide_matches_oracle(cfg):
+    log(f"start {cfg.name}")
+    inp = inputs.make_layer_inputs(cfg)
+    r = ref.decode_layer_cfg(cfg, inp.x, inp.pos, inp.k_cache, inp.v_cache, inp.weights)
+    gpu = run_gpu(cfg, inp)
+    full_check(cfg, inp, gpu, r)
+
+
+def test_batches_around_the_limit_on_one_handle():
+    """Steps of 40, 16, 17 and 3 sequences on one handle: each reads operands
+    that another layout and another batch left in the buffers."""
+    from paper_2607_11211_amd import layer as L
+    big = _cfg("w_mix", 108, 40, 512, 32, 8, 128, 7200, 60)
+    inp = inputs.make_layer_inputs(big)
+    lay = L.Layer(big, max_batch=64)
+    W = lay.pack({k: L.to_device(v) for k, v in inp.weights.items()})
+    Wf = ref.widen_weights(inp.weights)
+    for nb in (40, 16, 17, 3):
+        cfg = _cfg(f"w_mix{nb}", 108, nb, 512, 32, 8, 128, 7200, 60)
+        step = inputs.LayerInputs(cfg=cfg, x=inputs.make_x(cfg, seed=300 + nb), pos=inp.pos[:nb].copy(),
+                                  weights=inp.weights, k_cache=inp.k_cache[:nb].copy(),
+                                  v_cache=inp.v_cache[:nb].copy())
+        r = ref.decode_layer_cfg(cfg, step.x, step.pos, step.k_cache, step.v_cache, Wf)
+        log(f"start w_mix of {nb}")
+        full_check(cfg, step, run_gpu(cfg, step, layer=lay, weights=W), r)
+    W.free()
+    lay.destroy()
+
+
+def test_wide_replays_equal_eager():
+    """Graph replays with eager steps in between give the first eager step's
+    bits (operands and parts share buffers between the kernels of a step)."""
+    import torch
+    from paper_2607_11211_amd import layer as L
+    cfg = next(c for c in SHAPES if c.name == "w_parts_b49")
+    inp = inputs.make_layer_inputs(cfg)
+    lay = L.Layer(cfg)
+    W = lay.pack({k: L.to_device(v) for k, v in inp.weights.items()})
+    x = L.to_device(inp.x)
+    kc, vc = L.to_device(inp.k_cache), L.to_device(inp.v_cache)
+    y = torch.empty_like(x)
+    stream = torch.cuda.current_stream()
+    lay.step(W, x, inp.pos, kc, vc, y, stream)
+    torch.cuda.synchronize()
+    want = L.from_device(y)
+    g = torch.cuda.CUDAGraph()
+    s = torch.cuda.Stream()
+    s.wait_stream(stream)
+    with torch.cuda.stream(s):
+        with torch.cuda.graph(g, stream=s):
+            lay.step(W, x, inp.pos, kc, vc, y, s)
+    stream.wait_stream(s)
+    torch.cuda.synchronize()
+    for rep in range(4):
+        y.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(L.from_device(y), want), f"replay {rep} differs from the eager step"
+        lay.step(W, x, inp.pos, kc, vc, y, stream)
+        torch.cuda.synchronize()
+        assert np.array_equal(L.from_device(y), want)
+    del g
+    W.free()
+    lay.destroy()
