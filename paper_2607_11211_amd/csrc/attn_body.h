@@ -197,7 +197,8 @@ struct GlobalIO {
 // XCH: the contiguous loads and the LDS exchange (bf16 caches; xk, xv each
 // hold kThreads / kWave spans of 16 RC rows, one per wave); otherwise each
 // lane loads its quarter rows itself with plain loads.
-template <int D, int G, int NRING, bool PBF16, int KVF, class IO, bool XCH = false>
+// SMEM: the item's LDS (at least q, knew and vnew; run() needs AttnSmem).
+template <int D, int G, int NRING, bool PBF16, int KVF, class IO, bool XCH = false, class SMEM = AttnSmem<D, G, KVF>>
 struct AttnBody {
   using R = LaneRow<D, KVF>;
   using Chunk = typename R::Chunk;
@@ -209,7 +210,7 @@ struct AttnBody {
   static_assert(SEG == NC * R::EPC, "a lane's quarter row must be whole chunks");
   static_assert(G * HALF <= kThreads && D <= kThreads, "one prologue element per thread");
   static_assert(!XCH || (KVF == kKvBf16 && SPAN == kWave * NC), "the exchange covers a wave's rows in NC loads");
-  using Smem = AttnSmem<D, G, KVF>;
+  using Smem = SMEM;
 
   const AttnArgs& a;
   IO io;
@@ -315,8 +316,8 @@ struct AttnBody {
     }
   }
 
-  __device__ __forceinline__ void run(float kscale, float vscale) {
-    // ---- prologue: RoPE in double, rounding of the new K/V ------------------
+  // ---- RoPE in double, rounding of the new K/V, the append ------------------
+  __device__ __forceinline__ void prologue(float kscale, float vscale) {
     if (tid < G * HALF) {
       sm.q[ph][pj] = (float)((double)q0 * c_j - (double)q1 * s_j);
       sm.q[ph][pj + HALF] = (float)((double)q1 * c_j + (double)q0 * s_j);
@@ -340,6 +341,28 @@ struct AttnBody {
       uint8_t* dst = static_cast<uint8_t*>(isv ? a.v_cache : a.k_cache) + head_off + (size_t)P * D * kv_bytes<KVF>();
       reinterpret_cast<v4u*>(dst)[c] = val;
     }
+  }
+
+  // the test hook's q and k after RoPE, by the split that owns the new entry
+  __device__ __forceinline__ void write_dbg() {
+    if (a.dbg_qk && own_new) {
+      const int H = a.n_heads, Hkv = a.n_kv_heads;
+      float* dq = a.dbg_qk + (size_t)b * (H + Hkv) * D;
+      for (int i = tid; i < G * D; i += kThreads) dq[(size_t)g * G * D + i] = sm.q[i / D][i % D];
+      if (tid < HALF) {
+        // k and its cos/sin row again from memory (not held across the loop)
+        const size_t kg = (size_t)b * (H + 2 * Hkv) * D + (size_t)H * D + (size_t)g * D;
+        const double kk0 = io.qkv(a, kg + pj), kk1 = io.qkv(a, kg + pj + HALF);
+        const double c = a.rope_cos[(size_t)P * HALF + pj], sn = a.rope_sin[(size_t)P * HALF + pj];
+        float* dk = dq + (size_t)H * D + (size_t)g * D;
+        dk[pj] = (float)(kk0 * c - kk1 * sn);
+        dk[pj + HALF] = (float)(kk1 * c + kk0 * sn);
+      }
+    }
+  }
+
+  __device__ __forceinline__ void run(float kscale, float vscale) {
+    prologue(kscale, vscale);
     // this lane's quarter of the query heads: registers for one head, LDS
     // (read as a broadcast) for a group
     float qr[G == 1 ? SEG : 1];
@@ -428,22 +451,8 @@ struct AttnBody {
       update(kf, vf, true);
     }
 
-    // test hook: q and k after RoPE (fp32), written after the stream by the
-    // split that owns the new entry
-    if (a.dbg_qk && own_new) {
-      const int H = a.n_heads, Hkv = a.n_kv_heads;
-      float* dq = a.dbg_qk + (size_t)b * (H + Hkv) * D;
-      for (int i = tid; i < G * D; i += kThreads) dq[(size_t)g * G * D + i] = sm.q[i / D][i % D];
-      if (tid < HALF) {
-        // k and its cos/sin row again from memory (not held across the loop)
-        const size_t kg = (size_t)b * (H + 2 * Hkv) * D + (size_t)H * D + (size_t)g * D;
-        const double kk0 = io.qkv(a, kg + pj), kk1 = io.qkv(a, kg + pj + HALF);
-        const double c = a.rope_cos[(size_t)P * HALF + pj], sn = a.rope_sin[(size_t)P * HALF + pj];
-        float* dk = dq + (size_t)H * D + (size_t)g * D;
-        dk[pj] = (float)(kk0 * c - kk1 * sn);
-        dk[pj + HALF] = (float)(kk1 * c + kk0 * sn);
-      }
-    }
+    // test hook (after the stream)
+    write_dbg();
 
     // ---- merge: the 4 positions of each 16-lane row (DPP), then the rows --
     const int row = tid >> 4;

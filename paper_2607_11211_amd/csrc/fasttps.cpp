@@ -719,11 +719,16 @@ int fasttps_validate_step(const fasttps_config* cfg, const void* x, const int32_
 
 namespace {
 
-// Attention split: the tiles of 64 cached positions [0, pos) of every
-// (sequence, kv head) are dealt to nsplit interleaved splits of about
-// split_len positions, so that about `target` blocks carry the work (the new
-// entry at pos comes from registers, so it adds no tile of its own).
-int attention_splits(const fasttps_layer* l, const int32_t* pos, int32_t batch, int maxp) {
+// The attention of a step: which kernel (attention_on_mfma), and into how many
+// splits the tiles (64 cached positions, 128 on the matrix cores) of [0, pos)
+// of every (sequence, kv head) are dealt, of about split_len positions each,
+// so that about `target` blocks carry the work (the new entry at pos comes
+// from registers, so it adds no tile of its own).
+struct AttnPlan {
+  bool mfma;
+  int nsplit;
+};
+AttnPlan attention_plan(const fasttps_layer* l, const int32_t* pos, int32_t batch, int maxp, int kvf) {
   const fasttps_config& c = l->cfg;
   const int maxn = std::max(maxp, 1);
   long total = 0;
@@ -732,11 +737,19 @@ int attention_splits(const fasttps_layer* l, const int32_t* pos, int32_t batch, 
     total += pos[b];
     minp = std::min(minp, (int)pos[b]);
   }
+  AttnPlan p;
+  p.mfma = attention_on_mfma({c.n_heads / c.n_kv_heads, c.head_dim, kvf, l->p_bf16, batch, total * c.n_kv_heads});
+  const int tile = p.mfma ? kAttnMfmaTile : kAttnTile;
+  // ragged batches: more, shorter splits on the vector kernel only (matrix
+  // cores on MI355X, layer step, d 128, groups of four: 4 ragged sequences up
+  // to 8000 entries 53.8 us with 512 blocks, 57.1 with 2048; 32 up to 4000
+  // with an FP8 cache 87.2 against 93.1)
   const long target =
-      batch == 1 ? kTargetAttnBlocksOne : (minp == maxp ? 1 : kRaggedAttnFactor) * (long)kTargetAttnBlocks;
-  int split_len = round_up((int)std::min<long>((total * c.n_kv_heads + target - 1) / target, maxn), kAttnTile);
-  split_len = std::max(split_len, round_up(ceil_div(maxn, l->nsplit_cap), kAttnTile));
-  return ceil_div(maxn, split_len);
+      batch == 1 ? kTargetAttnBlocksOne : (minp == maxp || p.mfma ? 1 : kRaggedAttnFactor) * (long)kTargetAttnBlocks;
+  int split_len = round_up((int)std::min<long>((total * c.n_kv_heads + target - 1) / target, maxn), tile);
+  split_len = std::max(split_len, round_up(ceil_div(maxn, l->nsplit_cap), tile));
+  p.nsplit = ceil_div(maxn, split_len);
+  return p;
 }
 
 // Where a step keeps its fp32 intermediates: the layer handle's scratch, or
@@ -805,7 +818,8 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
 
   const bool wide = mfma && wide_pays(c, batch);
 
-  const int nsplit = attention_splits(l, pos, batch, maxp);
+  const AttnPlan plan = attention_plan(l, pos, batch, maxp, kvf);
+  const int nsplit = plan.nsplit;
 
   // one sequence: the whole step as one persistent kernel, on request
   // (FASTTPS_GEMM_FUSED), where it is built for the shape and the step is the
@@ -978,7 +992,10 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
   }
   used(0);
 
-  e = kvf == kKvBf16 ? launch_attention(aa, s, ev[1]) : launch_attention_kv8(aa, *sc, s, ev[1]);
+  if (plan.mfma)
+    e = launch_attention_mfma(aa, sc, s, ev[1]);
+  else
+    e = kvf == kKvBf16 ? launch_attention(aa, s, ev[1]) : launch_attention_kv8(aa, *sc, s, ev[1]);
   if (e != hipSuccess) return hip_fail(e, "attention launch");
   used(1);
   // one sequence on the vector path: the O projection merges the splits in
@@ -1071,7 +1088,7 @@ int fasttps_decode_step_noalloc(fasttps_layer* l, const fasttps_weights* w, cons
   int maxp = 0;
   const int st = check_step(l, w, x, pos, batch, k_cache, v_cache, y, &maxp);
   if (st) return st;
-  const int nsplit = attention_splits(l, pos, batch, maxp);
+  const int nsplit = attention_plan(l, pos, batch, maxp, kKvBf16).nsplit;
   const size_t need = noalloc_layout(l->cfg, batch, nsplit, nullptr, nullptr);
   if (need > kStaticScratchBytes)
     return fail(FASTTPS_ERR_UNSUPPORTED,

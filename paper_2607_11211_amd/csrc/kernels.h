@@ -157,7 +157,6 @@ constexpr int kPartLead = 4;
 
 struct AttnArgs {
   const float* qkv;        // [batch, (H + 2 H_kv) d] fp32, before RoPE
-  size_t qkv_part;         // large batches: floats from q|k|v to its second part, to be added (else 0)
   const double* rope_cos;  // [N_max, d/2]
   const double* rope_sin;  // [N_max, d/2]
   void* k_cache;           // [B, H_kv, N_max, d], bf16 or 8-bit codes
@@ -166,7 +165,6 @@ struct AttnArgs {
   float* o;                // [batch, H d] fp32
   uint16_t* o_operand;     // if set: o split for the MFMA O projection [kt][o_nbtc][64][8]
   int o_nbtc;
-  int o_wide;              // its layout: that of wide_operand_offset (large batches)
   int batch, n_heads, n_kv_heads, head_dim, max_seq;
   int nsplit, nsplit_cap;     // splits per (sequence, KV head): split s takes tiles s, s + nsplit, ...
   float scale;             // 1/sqrt(d)
@@ -176,6 +174,8 @@ struct AttnArgs {
   PosArray order;          // grid z -> sequence: the longest first, so the shortest blocks go last
   float* dbg_qk;           // test hook, null in normal steps: q and k after RoPE (fp32)
                            // [batch, (H + H_kv) d], q heads first
+  size_t qkv_part;         // large batches: floats from q|k|v to its second part, to be added (else 0)
+  int o_wide;              // large batches: o_operand in the layout of wide_operand_offset
 };
 // cache element formats (the values of the ABI's FASTTPS_KV_* constants)
 constexpr int kKvBf16 = 0, kKvFp8 = 1, kKvInt8 = 2;
@@ -189,6 +189,16 @@ struct KvScales {
 hipError_t launch_attention(const AttnArgs& a, hipStream_t s, KernelEvents ev = {});
 // the same over an 8-bit cache (a.kv_format kKvFp8 or kKvInt8)
 hipError_t launch_attention_kv8(const AttnArgs& a, const KvScales& sc, hipStream_t s, KernelEvents ev = {});
+// The same on the matrix cores (attn_mfma.hip), for both cache kinds: the
+// tiles dealt to the splits have kAttnMfmaTile positions. sc: an 8-bit cache's
+// scales.
+constexpr int kAttnMfmaTile = 128;
+struct AttnShape {
+  int group, head_dim, kv_format, p_bf16, batch;
+  long cached_rows;  // K rows of the step: the sequences' cached entries times the KV heads
+};
+bool attention_on_mfma(const AttnShape& t);
+hipError_t launch_attention_mfma(const AttnArgs& a, const KvScales* sc, hipStream_t s, KernelEvents ev = {});
 // combine the split partials into o
 hipError_t launch_attention_combine(const AttnArgs& a, hipStream_t s, KernelEvents ev = {});
 
