@@ -112,18 +112,6 @@ constexpr int kCombineThreads = 1024;
 constexpr int kCombineRegs = 32;  // splits per thread held in registers
 static_assert(kCombineThreads / 128 * kCombineRegs >= kMaxSplits, "one round of loads covers every split");
 
-// o at input k of sequence b for the MFMA O projection: its hi/lo bf16 split
-// in the lane order of the A operand (up to 16 sequences: row 2 (b % 8) +
-// level, k-group (k / 8) % 4 of k-tile k / 32, batch tile b / 8)
-__device__ __forceinline__ void put_o_operand(uint16_t* op, int nbtc, int wide, int b, int k, float v) {
-  const uint16_t hi = f32_to_bf16(v);
-  const uint16_t lo = f32_to_bf16(v - bf16_to_f32(hi));
-  const size_t at = wide ? wide_operand_offset(b, k, nbtc)
-                         : (((size_t)(k >> 5) * nbtc + b / 8) * kWave + 2 * (b % 8) + 16 * ((k >> 3) & 3)) * 8 + (k & 7);
-  op[at] = hi;
-  op[at + (wide ? kWave * 8 : 8)] = lo;
-}
-
 template <int D>
 __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(const float* __restrict__ part, int nsplit,
                                                                        int nsplit_cap, int n_heads,
@@ -171,7 +159,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(const flo
     for (int g2 = 0; g2 < NG; ++g2) O += osum[g2][tid];
     const float ov2 = O / L;
     o[((size_t)b * n_heads + h) * D + tid] = ov2;
-    if (o_operand) put_o_operand(o_operand, o_nbtc, o_wide, b, h * D + tid, ov2);
+    if (o_operand) attn::put_o_operand(o_operand, o_nbtc, o_wide, b, h * D + tid, ov2);
   }
 }
 
@@ -221,7 +209,7 @@ __global__ __launch_bounds__(kWave) void attn_combine_wave_kernel(const float* _
     if (e < D) {
       const float v = acc[i] / L;
       o[((size_t)b * n_heads + h) * D + e] = v;
-      if (o_operand) put_o_operand(o_operand, o_nbtc, o_wide, b, h * D + e, v);
+      if (o_operand) attn::put_o_operand(o_operand, o_nbtc, o_wide, b, h * D + e, v);
     }
   }
 }

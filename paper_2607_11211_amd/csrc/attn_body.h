@@ -172,12 +172,34 @@ __device__ __forceinline__ void tile_load_contig(v4u (&k)[NC], v4u (&v)[NC], con
   }
 }
 
+// o at input k of sequence b for the MFMA O projection: its hi/lo bf16 split
+// in the lane order of the A operand (up to 16 sequences: row 2 (b % 8) +
+// level, k-group (k / 8) % 4 of k-tile k / 32, batch tile b / 8)
+__device__ __forceinline__ void put_o_operand(uint16_t* op, int nbtc, int wide, int b, int k, float v) {
+  const uint16_t hi = f32_to_bf16(v);
+  const uint16_t lo = f32_to_bf16(v - bf16_to_f32(hi));
+  const size_t at = wide ? wide_operand_offset(b, k, nbtc)
+                         : (((size_t)(k >> 5) * nbtc + b / 8) * kWave + 2 * (b % 8) + 16 * ((k >> 3) & 3)) * 8 + (k & 7);
+  op[at] = hi;
+  op[at + (wide ? kWave * 8 : 8)] = lo;
+}
+
+// The finished output of one split that is the whole sequence (AttnArgs::direct):
+// element e of query head `head` of sequence b, from the split's o and l.
+__device__ __forceinline__ void put_direct(const AttnArgs& a, int b, int head, int e, int D, float o, float l) {
+  const float v = o / l;
+  const int k = head * D + e;
+  a.o[(size_t)b * a.n_heads * D + k] = v;
+  if (a.o_operand) put_o_operand(a.o_operand, a.o_nbtc, a.o_wide, b, k, v);
+}
+
 // Plain global-memory IO of the attention kernel. rec() is where the split's
 // record (m, l, -, -, o) of query head `head` of sequence b goes.
 // PARTS: q|k|v come in two parts (large batches). A template flag, so that the
 // count of loads ahead of the ring is known.
 template <bool PARTS = false>
 struct GlobalIO {
+  static constexpr bool kDirect = true;  // may write finished outputs (AttnArgs::direct)
   __device__ __forceinline__ float qkv(const AttnArgs& a, size_t i) const {
     return PARTS ? a.qkv[i] + a.qkv[i + a.qkv_part] : a.qkv[i];
   }
@@ -501,11 +523,16 @@ struct AttnBody {
       L += dpp_mov<kDppQuadXor1>(L);
       O += dpp_mov<kDppQuadXor1>(O);
       if (hr == 0 && i0 + tid / 2 < G * D) {
-        float* pr = io.rec(a, b, g * G + h, s, D);
-        io.part(pr + kPartLead + e, KVF == kKvBf16 ? O : O * vscale);  // an 8-bit cache's V scale
-        if (e == 0) {
-          io.part(pr, M);
-          io.part(pr + 1, L);
+        const float ov = KVF == kKvBf16 ? O : O * vscale;  // an 8-bit cache's V scale
+        if (IO::kDirect && a.direct) {
+          put_direct(a, b, g * G + h, e, D, ov, L);
+        } else {
+          float* pr = io.rec(a, b, g * G + h, s, D);
+          io.part(pr + kPartLead + e, ov);
+          if (e == 0) {
+            io.part(pr, M);
+            io.part(pr + 1, L);
+          }
         }
       }
     }

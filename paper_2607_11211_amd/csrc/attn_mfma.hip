@@ -323,8 +323,13 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a, float kscale, 
       const float ow = sm.o[w][0][h][e] + (finite_or_zero(sm.o[w][1][h][e]) + finite_or_zero(sm.o[w][2][h][e]));
       O = fmaf(ow, f, O);
     }
+    const float ov = KVF == kKvBf16 ? O : O * vscale;  // an 8-bit cache's V scale
+    if (a.direct) {
+      attn::put_direct(a, body.b, body.g * G + h, e, D, ov, L);
+      continue;
+    }
     float* pr = body.io.rec(a, body.b, body.g * G + h, body.s, D);
-    body.io.part(pr + kPartLead + e, KVF == kKvBf16 ? O : O * vscale);  // an 8-bit cache's V scale
+    body.io.part(pr + kPartLead + e, ov);
     if (e == 0) {
       body.io.part(pr, M);
       body.io.part(pr + 1, L);

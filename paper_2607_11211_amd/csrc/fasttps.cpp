@@ -40,6 +40,7 @@ constexpr int kTargetAttnBlocks = 512;
 // blocks it takes 12.8 us.
 constexpr int kTargetAttnBlocksOne = 256;
 constexpr int kRaggedAttnFactor = 4;
+constexpr int kOneSplitPairs = 256;  // one block per CU (attention_plan)
 constexpr int kAttnTile = 64;
 constexpr int kMaxSplits = 256;
 
@@ -749,6 +750,16 @@ AttnPlan attention_plan(const fasttps_layer* l, const int32_t* pos, int32_t batc
   int split_len = round_up((int)std::min<long>((total * c.n_kv_heads + target - 1) / target, maxn), tile);
   split_len = std::max(split_len, round_up(ceil_div(maxn, l->nsplit_cap), tile));
   p.nsplit = ceil_div(maxn, split_len);
+  // Where the (sequence, KV head) pairs alone fill the chip and the contexts
+  // are short, one split each: the attention then writes the finished o and
+  // the combine launch (4 us and its boundary) is gone. MI355X, layer step,
+  // several splits against one: Phi-3, 256 pairs, 300 entries 62.4 against
+  // 60.3 us, 20-400 ragged 65.5 / 59.6, 1000 70.8 / 69.0, 4000 118.1 / 120.4;
+  // 512 pairs, 100-2000 ragged 100.1 / 94.5, FP8 79.1 / 77.0 (256 pairs: 67.8
+  // / 70.4), 500-4096 ragged 128.4 / 129.2; Llama3-8B, 256 pairs, 20-400
+  // ragged 100.1 / 93.3, 512 pairs, 500-4096 ragged 214.7 / 220.6
+  const int pairs = batch * c.n_kv_heads;
+  if (pairs >= kOneSplitPairs && maxn <= (pairs < 2 * kOneSplitPairs ? 1024 : 2048)) p.nsplit = 1;
   return p;
 }
 
@@ -992,18 +1003,20 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
   }
   used(0);
 
+  // one sequence on the vector path: the O projection merges the splits in
+  // its prologue, one launch fewer (Phi-3 layer on MI355X, HIP graph: 60.1 ->
+  // 57.8 us per step at KV 4096, 54.5 -> 52.0 us at KV 1024); one split for
+  // each sequence: the attention writes the finished o; otherwise the combine
+  // kernel
+  const bool merge_in_o = !mfma && batch == 1 && oproj_merge_supported(c.n_heads, (int)d, nsplit, (int)D);
+  aa.direct = nsplit == 1 && !merge_in_o;
   if (plan.mfma)
     e = launch_attention_mfma(aa, sc, s, ev[1]);
   else
     e = kvf == kKvBf16 ? launch_attention(aa, s, ev[1]) : launch_attention_kv8(aa, *sc, s, ev[1]);
   if (e != hipSuccess) return hip_fail(e, "attention launch");
   used(1);
-  // one sequence on the vector path: the O projection merges the splits in
-  // its prologue, one launch fewer (Phi-3 layer on MI355X, HIP graph: 60.1 ->
-  // 57.8 us per step at KV 4096, 54.5 -> 52.0 us at KV 1024); otherwise the
-  // combine kernel
-  const bool merge_in_o = !mfma && batch == 1 && oproj_merge_supported(c.n_heads, (int)d, nsplit, (int)D);
-  if (!merge_in_o) {
+  if (!merge_in_o && !aa.direct) {
     if ((e = launch_attention_combine(aa, s, ev[2])) != hipSuccess) return hip_fail(e, "attention combine launch");
     used(2);
   }

@@ -176,6 +176,7 @@ struct AttnArgs {
                            // [batch, (H + H_kv) d], q heads first
   size_t qkv_part;         // large batches: floats from q|k|v to its second part, to be added (else 0)
   int o_wide;              // large batches: o_operand in the layout of wide_operand_offset
+  int direct;              // one split: write o and o_operand instead of a record to be combined
 };
 // cache element formats (the values of the ABI's FASTTPS_KV_* constants)
 constexpr int kKvBf16 = 0, kKvFp8 = 1, kKvInt8 = 2;

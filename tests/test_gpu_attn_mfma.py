@@ -58,6 +58,26 @@ def test_bf16_matches_oracle(cfg):
     full_check(cfg, inp, run_gpu(cfg, inp), r)
 
 
+# one split per (sequence, KV head): the attention writes the finished o, for
+# the vector and the matrix-core attention, the operand layouts of up to 16 and
+# of more sequences, and the vector projections
+DIRECT = [
+    _cfg("ad_g1_b16", 128, 16, 16, 64, tuple(range(0, 1024, 64))),
+    _cfg("ad_g4_b16", 129, 64, 16, 128, tuple(3 + 60 * i for i in range(16))),
+    _cfg("ad_g1_b64", 130, 8, 8, 96, tuple(1 + 31 * i for i in range(64)), 2049),
+]
+
+
+@pytest.mark.parametrize("cfg", DIRECT, ids=lambda c: c.name)
+@pytest.mark.parametrize("path", ["matrix", "vector"])
+def test_one_split_matches_oracle(cfg, path):
+    from paper_2607_11211_amd import layer as L
+    log(f"start {cfg.name} {path}")
+    inp = _inputs(cfg)
+    r = ref.decode_layer_cfg(cfg, inp.x, inp.pos, inp.k_cache, inp.v_cache, inp.weights)
+    full_check(cfg, inp, run_gpu(cfg, inp, gemm_path=L.GEMM_MATRIX if path == "matrix" else L.GEMM_VECTOR), r)
+
+
 KV8 = [
     _cfg("a8_g4_d64", 120, 8, 2, 64, EDGES),
     _cfg("a8_g4_d96", 121, 4, 1, 96, EDGES),
