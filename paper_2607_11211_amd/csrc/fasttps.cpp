@@ -24,8 +24,9 @@ constexpr uint64_t kLayerMagic = 0x4641535454505331ull;    // "FASTTPS1"
 constexpr uint64_t kWeightsMagic = 0x4641535454505357ull;  // "FASTTPSW"
 constexpr uint64_t kDeadMagic = 0xDEADDEADDEADDEADull;
 // attention blocks per step (256 CUs): 2 per CU (each lane with two tiles in
-// flight for one or two query heads per KV head, one for groups of four);
-// four times as many, shorter splits when the batch's positions are ragged.
+// flight for one or two query heads per KV head, one for groups of four); up
+// to four times as many, shorter splits when the batch's positions are ragged
+// (attention_plan).
 // Measured on MI355X: Phi-3 16-sequence ragged batch 101 -> 94 us and GQA
 // 4 x 32768 115 -> 103 us against 768 blocks throughout; then 512 blocks with
 // two tiles in flight against 768 with one: Phi-3 layer at KV 4096 61.7 ->
@@ -741,12 +742,18 @@ AttnPlan attention_plan(const fasttps_layer* l, const int32_t* pos, int32_t batc
   AttnPlan p;
   p.mfma = attention_on_mfma({c.n_heads / c.n_kv_heads, c.head_dim, kvf, l->p_bf16, batch, total * c.n_kv_heads});
   const int tile = p.mfma ? kAttnMfmaTile : kAttnTile;
-  // ragged batches: more, shorter splits on the vector kernel only (matrix
-  // cores on MI355X, layer step, d 128, groups of four: 4 ragged sequences up
-  // to 8000 entries 53.8 us with 512 blocks, 57.1 with 2048; 32 up to 4000
-  // with an FP8 cache 87.2 against 93.1)
-  const long target =
-      batch == 1 ? kTargetAttnBlocksOne : (minp == maxp || p.mfma ? 1 : kRaggedAttnFactor) * (long)kTargetAttnBlocks;
+  // Ragged batches on the vector kernel: two or four times the blocks, so that
+  // the short sequences' splits do not end early, from 1024 and 2048 positions
+  // a block up; below, the blocks' prologues and merges and the combine cost
+  // more (and on the matrix cores at any length). MI355X, layer step with 512 /
+  // 1024 / 2048 blocks: Phi-3, 4 sequences of 65-2500 entries (320 a block)
+  // 65.7 / 66.1 / 67.5 us, 3 of 500-8000 (800) 84.1 / 88.0 / 88.0, 16 of
+  // 65-2500 (1280) 101.0 / 101.6 / 108.2, 4 of 500-8000 (1060) 90.3 / 87.8 /
+  // 93.1, 16 of 500-8000 (4250) 186.8 / 185.8 / 184.7; matrix cores, d 128,
+  // groups of four, 4 of 500-8000 53.8 / 53.7 / 57.1
+  const long per_block = total * c.n_kv_heads / kTargetAttnBlocks;
+  const int ragged = minp == maxp || p.mfma || per_block < 1024 ? 1 : per_block < 2048 ? 2 : kRaggedAttnFactor;
+  const long target = batch == 1 ? kTargetAttnBlocksOne : ragged * (long)kTargetAttnBlocks;
   int split_len = round_up((int)std::min<long>((total * c.n_kv_heads + target - 1) / target, maxn), tile);
   split_len = std::max(split_len, round_up(ceil_div(maxn, l->nsplit_cap), tile));
   p.nsplit = ceil_div(maxn, split_len);
