@@ -140,41 +140,51 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a, float kscale, 
   Chunk kr[2][NS], vr[8];
   // position k (of 8) of this lane's group within a tile
   auto pos_of = [&](int k) { return 16 * (k / 4) + 4 * grp + k % 4; };
+  // byte offsets of this lane's rows within a tile: they change only when a
+  // tile reaches past the last cached entry (rows past it repeat it), so the
+  // loads of the others take no vector arithmetic (uniform base, lane offset)
+  unsigned koff[2], voff[8];
+  auto set_rows = [&](int last) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      koff[h] = (unsigned)(min(16 * h + n, last) * ROWB) + 16u * grp;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) voff[k] = (unsigned)(min(pos_of(k), last) * ROWB) + vch;
+  };
   auto load_k = [&](int t) {
-    const int last = body.last - t;
-    const char* base = Kc + (size_t)t * ROWB;  // uniform; a lane's offset stays within the tile
+    const char* base = Kc + (size_t)t * ROWB;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const char* row = base + (unsigned)(min(16 * h + n, last) * ROWB);
       if constexpr (KVF == kKvBf16) {
 #pragma unroll
-        for (int st = 0; st < NS; ++st) kr[h][st] = *reinterpret_cast<const Chunk*>(row + 16u * grp + 64 * st);
+        for (int st = 0; st < NS; ++st) kr[h][st] = *reinterpret_cast<const Chunk*>(base + 64 * st + koff[h]);
       } else {
         // 16 bytes serve two steps, so that a load takes 64 bytes of a row
 #pragma unroll
         for (int st = 0; st + 1 < NS; st += 2) {
-          const v4u c = *reinterpret_cast<const v4u*>(row + 16u * grp + 32 * st);
+          const v4u c = *reinterpret_cast<const v4u*>(base + 32 * st + koff[h]);
           kr[h][st] = Chunk{c.x, c.y};
           kr[h][st + 1] = Chunk{c.z, c.w};
         }
-        if constexpr (NS % 2) kr[h][NS - 1] = *reinterpret_cast<const Chunk*>(row + 8u * grp + 32 * (NS - 1));
+        if constexpr (NS % 2)
+          kr[h][NS - 1] = *reinterpret_cast<const Chunk*>(base + 32 * (NS - 1) + (koff[h] - 8u * grp));
       }
     }
     __builtin_amdgcn_sched_barrier(0);
   };
   auto load_v = [&](int t) {
-    const int last = body.last - t;
     const char* base = Vc + (size_t)t * ROWB;
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-      vr[k] = ld_stream(reinterpret_cast<const Chunk*>(base + (unsigned)(min(pos_of(k), last) * ROWB) + vch));
+    for (int k = 0; k < 8; ++k) vr[k] = ld_stream(reinterpret_cast<const Chunk*>(base + voff[k]));
     __builtin_amdgcn_sched_barrier(0);
   };
   // the first tile, unconditionally (a wave without one reads the last cached
   // entry, and slot 0 of an empty cache, and uses neither), so that the count
   // of loads behind the prologue's is known
-  load_k(min(t0, body.last));
-  load_v(min(t0, body.last));
+  const int tp = min(t0, body.last);
+  set_rows(body.last - tp);
+  load_k(tp);
+  load_v(tp);
   body.prologue(kscale, vscale);
 
   // this lane's column of q: its level of head n % 4 (zero past the group and
@@ -214,13 +224,27 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a, float kscale, 
                                                         0, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (!LAST) load_k(t + stride);
-    float sc[8], mx = -INFINITY;
+    if constexpr (!LAST) {
+      if (t + stride + kPos > P) set_rows(body.last - (t + stride));  // (uniform; the last refill)
+      load_k(t + stride);
+    }
+    float sc[8], tot = 0.f, mx = -INFINITY;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      float v = s2[k / 4][k % 4];
-      if (level > 0) v = finite_or_zero(v);
-      sc[k] = level_sum(v) * scale;
+      sc[k] = level_sum(s2[k / 4][k % 4]) * scale;
+      tot += sc[k];
+    }
+    if (__any(!(fabsf(tot) < INFINITY))) {
+      // some score is not finite: the lower levels' shares count only where
+      // they are (rare; checked on the sum, one comparison for eight)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const float v = s2[k / 4][k % 4];
+        sc[k] = level_sum(level > 0 ? finite_or_zero(v) : v) * scale;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
       if (LAST) sc[k] = t + pos_of(k) < P ? sc[k] : -INFINITY;
       mx = fmaxf(mx, sc[k]);
     }
