@@ -149,11 +149,22 @@ def _ptr(t) -> int:
     return 0 if t is None else int(t.data_ptr())
 
 
+_raw_stream = None  # (current device, raw current stream of a device), once torch's CUDA side is up
+
+
 def _stream_handle(stream) -> Optional[int]:
-    if stream is None:
+    """The stream's handle; None: the current stream of the current device (read
+    raw: building the Stream object that torch.cuda.current_stream returns costs
+    the host more than a launch)."""
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream or None
+    if _raw_stream is None:
         import torch
-        stream = torch.cuda.current_stream()
-    return stream.cuda_stream or None
+        torch.cuda.current_stream()  # initialises
+        _raw_stream = (torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    device, raw = _raw_stream
+    return raw(device()) or None
 
 
 class Weights:
