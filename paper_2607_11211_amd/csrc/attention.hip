@@ -35,6 +35,9 @@
 //     keeps an online-softmax state (m, l, o-quarter) per query head;
 //   * the block merges its lanes' states (DPP within each 16-lane row, then
 //     the 16 rows through LDS) and writes (m, l, o) for its split.
+// Groups of two and four query heads run on the matrix cores instead
+// (attn_mfma.hip; this kernel serves them only in the accuracy study), and so
+// do long batches over 8-bit caches.
 // The same kernel also serves an 8-bit cache (FP8 E4M3 or INT8 codes, one
 // scale per KV head for K and for V): a lane then loads d/4 bytes of a row,
 // decodes them with the hardware FP8 converts (or sign-extending byte
@@ -97,7 +100,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
 template <int D, int G, int KVF, bool PARTS>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void attn_split_kv8_kernel(
     AttnArgs a, KvScales sc) {
-  attn_split_body<D, G, (G <= 2 ? 2 : 1), false, KVF, false, PARTS>(a, sc.k[blockIdx.y], sc.v[blockIdx.y]);
+  attn_split_body<D, G, 2, false, KVF, false, PARTS>(a, sc.k[blockIdx.y], sc.v[blockIdx.y]);
 }
 
 // o[b, h] = sum_s e^{m_s - M} o_s / sum_s e^{m_s - M} l_s,  M = max_s m_s.
@@ -219,7 +222,8 @@ hipError_t launch_dg(const AttnArgs& a, hipStream_t s, KernelEvents ev) {
   // tiles in flight per lane: a tile is D / 8 registers of K and V; the
   // query quarter and the softmax state take (D / 4 + 2) G more. Two for one
   // or two query heads (103-226 VGPRs at d = 64-128: at least the two blocks
-  // per CU the split targets), one for groups of four (up to 256 VGPRs).
+  // per CU the split targets), one for groups of four (up to 256 VGPRs; the
+  // accuracy study only).
   // A group of four as two blocks of two heads each (two tiles in flight,
   // the pair reading the same K/V tiles at about the same time) was measured
   // slower on MI355X: GQA layer at 4 x 32768, attention 96.2 -> 116.8 us
@@ -230,13 +234,18 @@ hipError_t launch_dg(const AttnArgs& a, hipStream_t s, KernelEvents ev) {
   int maxp = 0;
   for (int b = 0; b < a.batch; ++b) maxp = a.pos.p[b] > maxp ? a.pos.p[b] : maxp;
   const int tiles = (maxp + attn::kTile - 1) / attn::kTile;
-  if constexpr (G <= 2) {
-    if ((tiles + a.nsplit - 1) / a.nsplit >= kXchMinTiles)
-      return a.p_bf16 ? ext_launch(attn_split_kernel<D, G, NRING, true, true, PARTS>, grid, dim3(kThreads), 0, s, ev, a)
-                      : ext_launch(attn_split_kernel<D, G, NRING, false, true, PARTS>, grid, dim3(kThreads), 0, s, ev, a);
+  const bool xch = G <= 2 && (tiles + a.nsplit - 1) / a.nsplit >= kXchMinTiles;
+  if constexpr (G == 1) {
+    if (!a.p_bf16)
+      return xch ? ext_launch(attn_split_kernel<D, G, NRING, false, true, PARTS>, grid, dim3(kThreads), 0, s, ev, a)
+                 : ext_launch(attn_split_kernel<D, G, NRING, false, false, PARTS>, grid, dim3(kThreads), 0, s, ev, a);
   }
-  return a.p_bf16 ? ext_launch(attn_split_kernel<D, G, NRING, true, false, PARTS>, grid, dim3(kThreads), 0, s, ev, a)
-                  : ext_launch(attn_split_kernel<D, G, NRING, false, false, PARTS>, grid, dim3(kThreads), 0, s, ev, a);
+  // groups run on the matrix cores (attn_mfma.hip), but for the accuracy study
+  if (!a.p_bf16) return hipErrorInvalidValue;
+  if constexpr (G <= 2) {
+    if (xch) return ext_launch(attn_split_kernel<D, G, NRING, true, true, PARTS>, grid, dim3(kThreads), 0, s, ev, a);
+  }
+  return ext_launch(attn_split_kernel<D, G, NRING, true, false, PARTS>, grid, dim3(kThreads), 0, s, ev, a);
 }
 
 template <int D, int G, bool PARTS>
@@ -254,7 +263,6 @@ hipError_t launch_kv8_d(const AttnArgs& a, const KvScales& sc, hipStream_t s, Ke
   switch (a.n_heads / a.n_kv_heads) {
     case 1: return a.qkv_part ? launch_kv8_dg<D, 1, true>(a, sc, s, ev) : launch_kv8_dg<D, 1, false>(a, sc, s, ev);
     case 2: return a.qkv_part ? launch_kv8_dg<D, 2, true>(a, sc, s, ev) : launch_kv8_dg<D, 2, false>(a, sc, s, ev);
-    case 4: return a.qkv_part ? launch_kv8_dg<D, 4, true>(a, sc, s, ev) : launch_kv8_dg<D, 4, false>(a, sc, s, ev);
     default: return hipErrorInvalidValue;
   }
 }

@@ -24,7 +24,7 @@ constexpr uint64_t kLayerMagic = 0x4641535454505331ull;    // "FASTTPS1"
 constexpr uint64_t kWeightsMagic = 0x4641535454505357ull;  // "FASTTPSW"
 constexpr uint64_t kDeadMagic = 0xDEADDEADDEADDEADull;
 // attention blocks per step (256 CUs): 2 per CU (each lane with two tiles in
-// flight for one or two query heads per KV head, one for groups of four); up
+// flight on the vector kernel); up
 // to four times as many, shorter splits when the batch's positions are ragged
 // (attention_plan).
 // Measured on MI355X: Phi-3 16-sequence ragged batch 101 -> 94 us and GQA

@@ -27,8 +27,15 @@
 // a matrix instruction are 16 sequences, and the two levels of the split are
 // two instructions into the same sums.
 // The QKV operand (x * gamma1, exact in two levels) and 1/rms(x) are prepared
-// once by a small kernel: built by every block, as the 16-sequence kernel does,
-// the conversion alone is 6.7 us of vector work per CU at 64 sequences.
+// once by a small kernel (3.5 us with its boundary): built by every block, as
+// the 16-sequence kernel does, the conversion alone is 6.7 us of vector work per
+// CU at 64 sequences, and its registers crowd the sums (QKV 22.5 us from the
+// prepared operand, 26.9-30.9 us built in place).
+// MI355X, kernel us, the 16-sequence kernels -> these: Phi-3 at 64 sequences QKV
+// 49.0 -> 22.5, O 24.9 -> 10.2, gate/up 75.9 -> 29.9, down 43.6 -> 18.7 (layer
+// 468 -> 372); Llama3-8B at 32 sequences 29.9 -> 15.3, 16.3 -> 10.4, 88.0 ->
+// 43.2 (6.4 TB/s with the launch), 48.5 -> 25.7. Weights or operand pointed at
+// one tile (timing only): gate/up at 64 sequences 16 and 21 us of the 30.
 #include "common.h"
 #include "kernels.h"
 
@@ -346,7 +353,9 @@ WideGeom wide_geom(WMode mode, int ns, int kt, int rh, int batch) {
   const int nstr0 = (ns + kWGrid - 1) / kWGrid;  // stripes per block, whole rows
   // Parts: the QKV projection has kWideQkvParts, the O and down projections
   // as many as bring the operand KB of a k-tile (2 nbt, spread over ks
-  // blocks' stripes) to the weight KB (ks nstr0 rh / 16)
+  // blocks' stripes) to the weight KB (ks nstr0 rh / 16): on MI355X at 64
+  // Phi-3 sequences O took 15.4 us and down 34.7 us in one part (sums stored
+  // by the block itself), 10.2 and 18.7 us in four
   int ks = mode == WMode::kQkv ? kWideQkvParts : 1;
   if (mode == WMode::kPart)
     while (ks < kWideMaxParts && 2 * g.nbt * 16 > ks * nstr0 * rh && kt >= 2 * ks * kWW) ks *= 2;
