@@ -284,8 +284,8 @@ FASTTPS_API int fasttps_set_mlp_path(fasttps_layer* layer, int32_t path);
  * the softmax weights to bf16 before the PV accumulation, as FlashAttention
  * does with its bf16 P (the softmax row sum stays fp32), so the attention
  * output error of the two can be compared over the context length (the
- * paper's Fig. 8 comparison, Section 4.4, OI and Accuracy). Off by default; a step with it on
- * is not the FastTPS step. */
+ * paper's Fig. 8 comparison, Section 4.4, OI and Accuracy). Steps over an 8-bit cache ignore
+ * it. Off by default; a step over a bf16 cache with it on is not the FastTPS step. */
 FASTTPS_API int fasttps_set_attention_p_bf16(fasttps_layer* layer, int32_t enable);
 
 /* Test hook: copy one of the step's fp32 intermediates from the handle's

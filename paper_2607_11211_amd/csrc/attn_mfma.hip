@@ -425,14 +425,17 @@ hipError_t launch_d(const AttnArgs& a, const KvScales* sc, hipStream_t s, Kernel
 //     55 down to 40 / 34
 //   one head over a bf16 cache: never (d 96, 8 x 4096 99.9 against 96.1)
 bool attention_on_mfma(const AttnShape& t) {
-  if (t.p_bf16) return false;
+  // the accuracy study (bf16 caches only) keeps the vector kernel, which rounds
+  // its weights; an 8-bit step ignores the switch
+  if (t.p_bf16 && t.kv_format == kKvBf16) return false;
   if (t.group == 4) return true;
   if (t.kv_format == kKvBf16) return t.group == 2;
   return t.batch >= 2 && t.cached_rows >= (1L << 18) && (t.group == 2 || t.head_dim > 64);
 }
 
 hipError_t launch_attention_mfma(const AttnArgs& a, const KvScales* sc, hipStream_t s, KernelEvents ev) {
-  if (a.nsplit < 1 || a.nsplit > a.nsplit_cap || a.p_bf16) return hipErrorInvalidValue;
+  if (a.nsplit < 1 || a.nsplit > a.nsplit_cap) return hipErrorInvalidValue;
+  if (a.p_bf16 && a.kv_format == kKvBf16) return hipErrorInvalidValue;
   if (a.kv_format != kKvBf16 && (!sc || a.n_kv_heads > kMaxKvHeads)) return hipErrorInvalidValue;
   switch (a.head_dim) {
     case 64: return launch_d<64>(a, sc, s, ev);

@@ -156,3 +156,22 @@ def test_vector_kernel_still_serves_groups():
     torch.cuda.synchronize()
     got["_weights"].free()
     lay.destroy()
+
+
+@pytest.mark.parametrize("fmt", inputs.KV8_FORMATS)
+@pytest.mark.parametrize("index,heads,kv", [(131, 4, 4), (132, 4, 2), (133, 8, 2)], ids=["g1", "g2", "g4"])
+def test_study_switch_leaves_kv8_alone(index, heads, kv, fmt):
+    """The accuracy study's switch is about bf16 caches: a step over an 8-bit
+    cache runs with it on as without it, for every group size."""
+    from paper_2607_11211_amd import layer as L
+    from test_gpu_kv8 import run_case
+    cfg = _cfg("a8_switch", index, heads, kv, 64, (130, 0, 33))
+    inp = _inputs(cfg)
+    lay = L.Layer(cfg)
+    W = lay.pack({k: L.to_device(v) for k, v in inp.weights.items()})
+    off, _ = run_case(cfg, inp, fmt, layer=lay, weights=W)
+    lay.set_attention_p_bf16(True)
+    on, _ = run_case(cfg, inp, fmt, layer=lay, weights=W)
+    assert np.array_equal(on["y"], off["y"])
+    W.free()
+    lay.destroy()
