@@ -132,6 +132,12 @@ bool wide_pays(const fasttps_config& c, int batch) {
   const size_t weight_bytes = 2 * (D * (q + 2 * kv) + D * q + 3 * D * c.intermediate);
   return batch >= kWideMinBatch && weight_bytes * ((batch - 1) / 16) >= kWideMinReread;
 }
+// the largest step of the layer whose projections run on mfma_proj.hip
+int max_proj_batch(const fasttps_config& c) {
+  int b = c.max_batch;
+  while (wide_pays(c, b)) --b;
+  return b;
+}
 
 // test-hook buffers a step wrote (fasttps_layer::dbg_written)
 constexpr int kDbgQk = 1, kDbgNorm = 2;
@@ -368,7 +374,7 @@ int fasttps_layer_create(const fasttps_config* cfg, fasttps_layer** out) {
     const TileDims* tds[3] = {&lt.o, &lt.gu, &lt.down};
     for (int i = 0; i < 3; ++i) {
       size_t f = 0, t = 0;
-      mfma_split_need(i + 1, tds[i]->ns, tds[i]->kt, tds[i]->rh, std::min(B, kWideMinBatch - 1), &f, &t);
+      mfma_split_need(i + 1, tds[i]->ns, tds[i]->kt, tds[i]->rh, max_proj_batch(c), &f, &t);
       split_floats = std::max(split_floats, f);
       split_tickets = std::max(split_tickets, t);
       if (i != 1)

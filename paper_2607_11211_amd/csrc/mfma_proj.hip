@@ -679,17 +679,13 @@ hipError_t launch_mmode(const MfmaArgs& a_in, hipStream_t s, KernelEvents ev) {
   if (a.rh < 2 || a.rh > 16 || a.rh % 2 != 0) return hipErrorInvalidValue;
   if (MODE == MMode::kGateUp && a.ns_in > kMaxStripesIn) return hipErrorInvalidValue;
   const int nbt = nbt_of(a.batch);
-  SplitGeom g = split_geom(MODE, a.ns, a.kt, a.rh, nbt);
+  const SplitGeom g = split_geom(MODE, a.ns, a.kt, a.rh, nbt);
   const size_t nout = (size_t)nbt * kSeqTile * 16;
   const size_t ny = (a.batch + kGroupSeq - 1) / kGroupSeq;
+  // (a layer's scratch covers every step that runs here: its need grows with the batch)
   if (g.ks > 1 && (!a.kpart || !a.tickets || a.kpart_cap < ny * g.ngr * g.ks * g.nstr_max * nout ||
-                   a.tickets_cap < ny * g.ngr)) {
-    g.ks = 1;  // no scratch for the parts: whole rows per block
-    g.ngr = a.ns < kMGrid ? a.ns : kMGrid;
-    g.ktq = a.kt;
-    g.nt = a.nt;
-    g.nstr_max = (a.ns + g.ngr - 1) / g.ngr;
-  }
+                   a.tickets_cap < ny * g.ngr))
+    return hipErrorInvalidValue;
   a.ks = g.ks;
   a.ktq = g.ktq;
   a.nt = g.nt;

@@ -63,6 +63,9 @@ SHAPES = [
     # split down projection over 33 stripes of 8 rows (hidden 264) and two grid rows (20 sequences)
     LayerConfig(name="m_split_down_b20", index=59, batch=20, hidden=264, n_heads=4, n_kv_heads=4, head_dim=64,
                 intermediate=4096, rope_base=10000.0, max_seq=120, pos=tuple((13 * i) % 117 for i in range(20))),
+    # the same over 32 stripes of 16 rows and three grid rows (40 sequences)
+    LayerConfig(name="m_split_down_b40", index=63, batch=40, hidden=512, n_heads=4, n_kv_heads=4, head_dim=64,
+                intermediate=4096, rope_base=10000.0, max_seq=90, pos=tuple((13 * i) % 87 for i in range(40))),
     # split O projection (32 x 128 = 4096 inputs, 16 stripes): its last block writes h1, the gate/up
     # operand and the sums of h1^2
     LayerConfig(name="m_split_o_b12", index=60, batch=12, hidden=256, n_heads=32, n_kv_heads=8, head_dim=128,
@@ -163,12 +166,14 @@ def test_path_hook_errors():
     two.destroy()
 
 
-def test_split_graph_replays_equal_eager():
+@pytest.mark.parametrize("name", ["m_split_down_b16", "m_split_down_b20", "m_split_down_b40"])
+def test_split_graph_replays_equal_eager(name):
     """The split projections' tickets are left at zero by every launch: graph
-    replays and eager steps in between give the first eager step's bits."""
+    replays and eager steps in between give the first eager step's bits, with
+    one and with several rows of tickets."""
     import torch
     from paper_2607_11211_amd import layer as L
-    cfg = next(c for c in SHAPES if c.name == "m_split_down_b16")
+    cfg = next(c for c in SHAPES if c.name == name)
     inp = inputs.make_layer_inputs(cfg)
     lay = L.Layer(cfg)
     lay.set_gemm_path(L.GEMM_MATRIX)
