@@ -122,11 +122,14 @@ constexpr int kInterlaceTile = 1;
 // 16 sequences, those of mfma_wide.hip once, at three launches more (the QKV
 // operand and two sums of parts, about 9 us). The line lies where what is
 // read again costs as much: on MI355X, layer steps at 64 cached entries,
-// mfma_proj against mfma_wide: hidden 512 (6 MB a layer) at 64 sequences 36.3
-// against 39.6 us, hidden 1024 (26 MB) 36.6 against 37.6 us at 32 and 49.4
-// against 41.6 at 33, Phi-3 (227 MB) 122.3 against 82.8 us at 32 and 233.5
-// against 109.1 at 64.
-constexpr size_t kWideMinReread = size_t(32) << 20;
+// mfma_proj against mfma_wide (reread): hidden 256, MLP 4096 at 32 and 48
+// sequences (7 and 14 MB) 27.3 against 29.5 and 32.8 against 33.0 us; hidden 512,
+// MLP 2048 at 64 (25.2 MB) 35.7 against 36.4; hidden 512, MLP 4096 at 32 and 33
+// (15 and 29 MB) 31.1 against 31.5 and 40.9 against 34.6; hidden 1024, MLP 2816
+// at 32 (25.7 MB) 35.1 against 35.5; hidden 512, MLP 8192 at 17 (27.3 MB) 37.6
+// against 34.3; hidden 1024, MLP 4096 at 17 (33.6 MB) 37.2 against 34.6; Phi-3
+// (227 MB) 122.3 against 82.8 at 32 and 233.5 against 109.1 at 64.
+constexpr size_t kWideMinReread = size_t(25) << 20;
 bool wide_pays(const fasttps_config& c, int batch) {
   const size_t D = c.hidden, q = (size_t)c.n_heads * c.head_dim, kv = (size_t)c.n_kv_heads * c.head_dim;
   const size_t weight_bytes = 2 * (D * (q + 2 * kv) + D * q + 3 * D * c.intermediate);

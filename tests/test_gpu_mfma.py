@@ -63,8 +63,8 @@ SHAPES = [
     # split down projection over 33 stripes of 8 rows (hidden 264) and two grid rows (20 sequences)
     LayerConfig(name="m_split_down_b20", index=59, batch=20, hidden=264, n_heads=4, n_kv_heads=4, head_dim=64,
                 intermediate=4096, rope_base=10000.0, max_seq=120, pos=tuple((13 * i) % 117 for i in range(20))),
-    # the same over 32 stripes of 16 rows and three grid rows (40 sequences)
-    LayerConfig(name="m_split_down_b40", index=63, batch=40, hidden=512, n_heads=4, n_kv_heads=4, head_dim=64,
+    # the same over 16 stripes of 16 rows and three grid rows (40 sequences)
+    LayerConfig(name="m_split_down_b40", index=63, batch=40, hidden=256, n_heads=4, n_kv_heads=4, head_dim=64,
                 intermediate=4096, rope_base=10000.0, max_seq=90, pos=tuple((13 * i) % 87 for i in range(40))),
     # split O projection (32 x 128 = 4096 inputs, 16 stripes): its last block writes h1, the gate/up
     # operand and the sums of h1^2

@@ -29,7 +29,7 @@ def _cfg(name, index, batch, hidden, heads, kv, d, inter, max_seq=40):
                        pos=tuple((7 * i + 3) % max_seq for i in range(batch)))
 
 
-# sizes past the line of the dispatch (32 MB of weights read again by the kernels of 16 sequences)
+# sizes past the line of the dispatch (25 MB of weights read again by the kernels of 16 sequences)
 SHAPES = [
     # one sequence past the limit; hidden 776 pads stripes and k-tiles
     _cfg("w_b17", 100, 17, 776, 8, 8, 96, 6408, 130),
