@@ -36,8 +36,9 @@
 //   * the block merges its lanes' states (DPP within each 16-lane row, then
 //     the 16 rows through LDS) and writes (m, l, o) for its split.
 // Groups of two and four query heads run on the matrix cores instead
-// (attn_mfma.hip; this kernel serves them only in the accuracy study), and so
-// do long batches over 8-bit caches.
+// (attn_mfma.hip; this kernel serves them in the accuracy study, and groups of
+// two at d = 64 over short contexts), and so do long batches over 8-bit caches
+// (attention_on_mfma).
 // The same kernel also serves an 8-bit cache (FP8 E4M3 or INT8 codes, one
 // scale per KV head for K and for V): a lane then loads d/4 bytes of a row,
 // decodes them with the hardware FP8 converts (or sign-extending byte
@@ -235,12 +236,12 @@ hipError_t launch_dg(const AttnArgs& a, hipStream_t s, KernelEvents ev) {
   for (int b = 0; b < a.batch; ++b) maxp = a.pos.p[b] > maxp ? a.pos.p[b] : maxp;
   const int tiles = (maxp + attn::kTile - 1) / attn::kTile;
   const bool xch = G <= 2 && (tiles + a.nsplit - 1) / a.nsplit >= kXchMinTiles;
-  if constexpr (G == 1) {
+  if constexpr (G == 1 || (G == 2 && D == 64)) {
     if (!a.p_bf16)
       return xch ? ext_launch(attn_split_kernel<D, G, NRING, false, true, PARTS>, grid, dim3(kThreads), 0, s, ev, a)
                  : ext_launch(attn_split_kernel<D, G, NRING, false, false, PARTS>, grid, dim3(kThreads), 0, s, ev, a);
   }
-  // groups run on the matrix cores (attn_mfma.hip), but for the accuracy study
+  // the other groups run on the matrix cores (attn_mfma.hip), but for the accuracy study
   if (!a.p_bf16) return hipErrorInvalidValue;
   if constexpr (G <= 2) {
     if (xch) return ext_launch(attn_split_kernel<D, G, NRING, true, true, PARTS>, grid, dim3(kThreads), 0, s, ev, a);

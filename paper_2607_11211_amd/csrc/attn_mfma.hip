@@ -415,22 +415,40 @@ hipError_t launch_d(const AttnArgs& a, const KvScales* sc, hipStream_t s, Kernel
 // (this kernel against the vector kernel, us a layer step; D the hidden size):
 //   groups of four, every cache: D 4096, d 128, 8 x 4096 entries 61.1 against
 //     69.3 (bf16), 56.1 against 59.8 (FP8); 1 x 8000 43.1 against 45.4
-//   groups of two, bf16: d 128, 8 x 4096 83.6 against 86.7; 1 x 8000 50.0
-//     against 52.7; d 64, 1 x 300 26.1 against 25.9, 1 x 8000 equal
+//   groups of two, bf16, d 96 and 128: d 128, 8 x 4096 83.6 against 86.7; 1 x
+//     8000 50.0 against 52.7; D 1536, 16 KV heads, d 96, 1 x 16 26.7 against 26.9
+//   groups of two, bf16, d 64: this kernel's prologue (the levels of q) costs
+//     0.5 us more, which shorter loops do not win back; except between 65 and
+//     128 positions, which are one tile here and two there (no combine launch).
+//     D 1536, 8 and 16 KV heads: 1 x 200 23.8 against 23.3 and 25.2 against 24.7, 1 x
+//     700 24.1 against 24.6 and 26.1 against 27.1; 4 x 64 30.7 against 30.0, 4 x 128
+//     30.7 against 32.5; 4 x 200 (6400 rows) 33.2 against 32.6, 16 KV heads 8 x 500
+//     (64000) 36.5 against 35.9, 16 x 500 (128000) 38.7 against 40.2
 //   8-bit caches in smaller groups: from two sequences with 2^18 cached rows
 //     up (about 512 positions per block), and not one head at d = 64 (half of
 //     a load's lanes repeat): groups of two, d 128, 32 ragged 94.2 against
 //     113.9; one head, d 96, 16 x 4096 109 against 114, 4 x 1000 40.7 against
 //     39.9; d 64, 4 ragged INT8 44.8 against 41.9; at one sequence from 57 /
 //     55 down to 40 / 34
+//   groups of two at d 64 over 8-bit caches: from about 1090 positions per block
+//     up. FP8 / INT8, 16 KV heads, D 2048, 8 x 4000 entries 48.2 / 49.8 against 47.9 /
+//     48.2, 4 of 500-16000 (546k rows) 49.5 / 51.4 against 52.4 / 52.3; 32 KV heads, D
+//     4096, 8 x 2100 96.6 / 97.8 against 95.1 / 95.7, 64 x 300 157.4 / 159.6 against
+//     159.3 / 160.2, 8 x 4000 105.6 / 107.2 against 110.9 / 111.2
 //   one head over a bf16 cache: never (d 96, 8 x 4096 99.9 against 96.1)
 bool attention_on_mfma(const AttnShape& t) {
   // the accuracy study (bf16 caches only) keeps the vector kernel, which rounds
   // its weights; an 8-bit step ignores the switch
   if (t.p_bf16 && t.kv_format == kKvBf16) return false;
   if (t.group == 4) return true;
-  if (t.kv_format == kKvBf16) return t.group == 2;
-  return t.batch >= 2 && t.cached_rows >= (1L << 18) && (t.group == 2 || t.head_dim > 64);
+  if (t.kv_format == kKvBf16) {
+    if (t.group != 2 || t.head_dim > 64) return t.group == 2;
+    if (t.batch == 1) return t.max_pos > 2 * kAttnMfmaTile;
+    return t.cached_rows > (1L << 16) || (t.max_pos > kAttnMfmaTile / 2 && t.max_pos <= kAttnMfmaTile);
+  }
+  if (t.batch < 2 || t.cached_rows < (1L << 18)) return false;
+  if (t.head_dim > 64) return true;
+  return t.group == 2 && t.cached_rows >= (17L << 15);
 }
 
 hipError_t launch_attention_mfma(const AttnArgs& a, const KvScales* sc, hipStream_t s, KernelEvents ev) {

@@ -749,7 +749,8 @@ AttnPlan attention_plan(const fasttps_layer* l, const int32_t* pos, int32_t batc
     minp = std::min(minp, (int)pos[b]);
   }
   AttnPlan p;
-  p.mfma = attention_on_mfma({c.n_heads / c.n_kv_heads, c.head_dim, kvf, l->p_bf16, batch, total * c.n_kv_heads});
+  p.mfma = attention_on_mfma(
+      {c.n_heads / c.n_kv_heads, c.head_dim, kvf, l->p_bf16, batch, maxp, total * c.n_kv_heads});
   const int tile = p.mfma ? kAttnMfmaTile : kAttnTile;
   // Ragged batches on the vector kernel: two or four times the blocks, so that
   // the short sequences' splits do not end early, from 1024 and 2048 positions

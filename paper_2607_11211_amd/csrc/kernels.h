@@ -196,6 +196,7 @@ hipError_t launch_attention_kv8(const AttnArgs& a, const KvScales& sc, hipStream
 constexpr int kAttnMfmaTile = 128;
 struct AttnShape {
   int group, head_dim, kv_format, p_bf16, batch;
+  int max_pos;       // cached entries of the longest sequence
   long cached_rows;  // K rows of the step: the sequences' cached entries times the KV heads
 };
 bool attention_on_mfma(const AttnShape& t);

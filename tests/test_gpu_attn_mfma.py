@@ -47,6 +47,14 @@ BF16 = [
     # one sequence in many splits, and a batch whose short sequences leave splits empty
     _cfg("am_g4_one", 116, 4, 1, 64, (9000,)),
     _cfg("am_g2_ragged", 117, 16, 8, 128, (5, 4000, 130, 2049)),
+    # groups of two at d = 64 on both sides of their lines: one sequence of up to 256 positions
+    # (vector) and more, batches of up to 64 (vector), 128, and of 2^16 rows (vector) and one more
+    _cfg("am_g2_d64_one256", 134, 4, 2, 64, (256,)),
+    _cfg("am_g2_d64_one257", 135, 4, 2, 64, (257,)),
+    _cfg("am_g2_d64_64", 136, 4, 2, 64, (64, 0, 17)),
+    _cfg("am_g2_d64_65", 137, 4, 2, 64, tuple(e for e in EDGES if e <= 128) + (65,)),
+    _cfg("am_g2_d64_2p16", 138, 64, 32, 64, (1900, 148)),
+    _cfg("am_g2_d64_2p16_1", 139, 64, 32, 64, (1900, 149)),
 ]
 
 
@@ -82,12 +90,15 @@ KV8 = [
     _cfg("a8_g4_d64", 120, 8, 2, 64, EDGES),
     _cfg("a8_g4_d96", 121, 4, 1, 96, EDGES),
     _cfg("a8_g4_d128", 122, 8, 2, 128, EDGES),
-    # smaller groups take this kernel from 2^18 cached rows up
+    # smaller groups take this kernel from 2^18 cached rows up (at d = 64 from 17 * 2^15)
     _cfg("a8_g1_d96", 123, 32, 32, 96, (4099, 4110)),
     _cfg("a8_g1_d128", 124, 32, 32, 128, (8193, 33)),
     _cfg("a8_g2_d64", 125, 64, 32, 64, (127, 8200, 1)),
     _cfg("a8_g2_d96", 126, 32, 16, 96, (8192, 8193)),
     _cfg("a8_g2_d128", 127, 64, 32, 128, (4096, 4097)),
+    # groups of two at d = 64: one row short of their line (vector) and on it
+    _cfg("a8_g2_d64_below", 140, 64, 32, 64, (127, 17279, 1)),
+    _cfg("a8_g2_d64_line", 141, 64, 32, 64, (127, 17280, 1)),
 ]
 
 
