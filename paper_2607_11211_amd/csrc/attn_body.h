@@ -200,6 +200,7 @@ __device__ __forceinline__ void put_direct(const AttnArgs& a, int b, int head, i
 template <bool PARTS = false>
 struct GlobalIO {
   static constexpr bool kDirect = true;  // may write finished outputs (AttnArgs::direct)
+  static constexpr bool kParts = PARTS;
   __device__ __forceinline__ float qkv(const AttnArgs& a, size_t i) const {
     return PARTS ? a.qkv[i] + a.qkv[i + a.qkv_part] : a.qkv[i];
   }
@@ -365,8 +366,10 @@ struct AttnBody {
     }
   }
 
-  // the test hook's q and k after RoPE, by the split that owns the new entry
+  // for the test hooks, by the split that owns the new entry: whether this
+  // sequence's q|k|v came in two parts, and q and k after RoPE
   __device__ __forceinline__ void write_dbg() {
+    if (a.qkv_split && own_new && g == 0 && tid == 0) a.qkv_split[b] = IO::kParts;
     if (a.dbg_qk && own_new) {
       const int H = a.n_heads, Hkv = a.n_kv_heads;
       float* dq = a.dbg_qk + (size_t)b * (H + Hkv) * D;
@@ -473,7 +476,7 @@ struct AttnBody {
       update(kf, vf, true);
     }
 
-    // test hook (after the stream)
+    // test hooks (after the stream)
     write_dbg();
 
     // ---- merge: the 4 positions of each 16-lane row (DPP), then the rows --

@@ -215,13 +215,15 @@ struct fasttps_layer {
   float* split_part = nullptr;    // the split projections' partial sums
   unsigned* split_tickets = nullptr;  // and their row groups' tickets (zero between steps)
   size_t split_part_cap = 0, split_tickets_cap = 0;
+  // layers with steps on mfma_wide.hip: per sequence (device), whether the
+  // last step left its q|k|v in two parts, max_batch sequences apart
+  int* qkv_split = nullptr;
   int gemm_path = FASTTPS_GEMM_AUTO;
   // the MLP as one kernel with h^sm on chip (fasttps_set_mlp_path): its
   // partial sums of y [slices][max_batch][D], allocated when first selected
   int mlp_path = FASTTPS_MLP_SPLIT;
   int weight_layout = FASTTPS_WEIGHTS_ROWS_AND_TILES;  // how later packs store the projections
   float* mlp_part = nullptr;
-  size_t qkv_part = 0;         // the last step's q|k|v came in two parts this far apart (else 0)
   bool mlp_a_written = false;  // the last step stored h^sm (FASTTPS_DBG_MLP_A)
   // the fused kernel's phase hand-over: per-block phase flags, the epoch of
   // the last completed launch, the count of bounded waits that ran out
@@ -369,6 +371,7 @@ int fasttps_layer_create(const fasttps_config* cfg, fasttps_layer** out) {
   }
 
   const bool mfma = B > 1;
+  const bool wide = wide_pays(c, B);  // the larger steps run on mfma_wide.hip
   const int nbtc = 2 * ceil_div(B, 16);
   const LayerTiles lt = layer_tiles(c);
   // the split projections run one after another: one scratch serves them all
@@ -380,15 +383,15 @@ int fasttps_layer_create(const fasttps_config* cfg, fasttps_layer** out) {
       mfma_split_need(i + 1, tds[i]->ns, tds[i]->kt, tds[i]->rh, max_proj_batch(c), &f, &t);
       split_floats = std::max(split_floats, f);
       split_tickets = std::max(split_tickets, t);
-      if (i != 1)
+      if (wide && i != 1)
         split_floats = std::max(split_floats,
                                 wide_part_floats(tds[i]->ns, tds[i]->kt, tds[i]->rh, c.hidden, B));
     }
   }
-  size_t sizes[17] = {
+  size_t sizes[18] = {
       cs.size() * sizeof(double),
       sn.size() * sizeof(double),
-      (size_t)B * qkv_rows * sizeof(float) * (B >= kWideMinBatch ? kWideQkvParts : 1),
+      (size_t)B * qkv_rows * sizeof(float) * (wide ? kWideQkvParts : 1),
       (size_t)B * c.n_heads * nsplit_cap * (d + kPartLead) * sizeof(float),
       (size_t)B * c.n_heads * d * sizeof(float),
       (size_t)B * c.hidden * sizeof(float),
@@ -403,9 +406,10 @@ int fasttps_layer_create(const fasttps_config* cfg, fasttps_layer** out) {
       (size_t)B * c.hidden * sizeof(float),
       split_floats * sizeof(float),
       split_tickets * sizeof(unsigned),
+      wide ? (size_t)B * sizeof(int) : 0,
   };
-  size_t total = 0, offs[17];
-  for (int i = 0; i < 17; ++i) {
+  size_t total = 0, offs[18];
+  for (int i = 0; i < 18; ++i) {
     offs[i] = total;
     total += align256(sizes[i]);
   }
@@ -455,6 +459,7 @@ int fasttps_layer_create(const fasttps_config* cfg, fasttps_layer** out) {
       l->split_tickets_cap = split_tickets;
     }
   }
+  if (wide) l->qkv_split = reinterpret_cast<int*>(base + offs[17]);
   l->fused_flags = reinterpret_cast<unsigned*>(base + offs[11]);
   l->fused_epoch = l->fused_flags + kFusedPhases * kFusedBlocks;
   l->fused_err = reinterpret_cast<int*>(l->fused_epoch + 1);
@@ -930,7 +935,8 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
 
   AttnArgs aa{};
   aa.qkv = S.qkv;
-  aa.qkv_part = wide ? (size_t)batch * qa.rows : 0;
+  aa.qkv_part = wide ? (size_t)c.max_batch * qa.rows : 0;
+  aa.qkv_split = S.noalloc ? nullptr : l->qkv_split;
   aa.rope_cos = l->rope_cos;
   aa.rope_sin = l->rope_sin;
   aa.k_cache = static_cast<uint16_t*>(k_cache);
@@ -958,7 +964,6 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
 
   if (!S.noalloc) {
     l->dbg_written = 0;
-    l->qkv_part = aa.qkv_part;
     l->mlp_a_written = !mlp_fused;  // h^sm is stored by every path but the fused MLP
   }
   if (fused) {
@@ -1008,6 +1013,7 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
     m.x_bf16 = xb;
     m.gamma = w->attn_norm;
     m.out = S.qkv;
+    m.part_seqs = c.max_batch;
     if (wide) {
       // the QKV operand and 1/rms(x) in buffers the O projection fills later
       // (the gate/up operand has the same inputs)
@@ -1190,9 +1196,10 @@ int fasttps_debug_read(fasttps_layer* l, int32_t which, int32_t batch, void* dst
   }
   n *= (size_t)batch * sizeof(float);
   if (bytes != n) return fail(FASTTPS_ERR_INVALID_ARG, "bytes %zu != %zu", bytes, n);
-  if (which == FASTTPS_DBG_QKV && l->qkv_part) {
-    const hipError_t e = launch_wide_qkv_sum(l->qkv, l->qkv_part, n / sizeof(float), static_cast<float*>(dst),
-                                             static_cast<hipStream_t>(stream));
+  if (which == FASTTPS_DBG_QKV && l->qkv_split) {
+    const int rows = (c.n_heads + 2 * c.n_kv_heads) * c.head_dim;
+    const hipError_t e = launch_wide_qkv_sum(l->qkv, (size_t)c.max_batch * rows, l->qkv_split, rows, batch,
+                                             static_cast<float*>(dst), static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "debug copy");
     return FASTTPS_OK;
   }

@@ -81,7 +81,7 @@ struct StageIO {
 // into its LDS slot
 template <int G>
 struct SubAttnIO {
-  static constexpr bool kDirect = false;
+  static constexpr bool kDirect = false, kParts = false;
   float* slot;  // [G][D + kPartLead]
   __device__ __forceinline__ float qkv(const AttnArgs& a, size_t i) const { return ld_c(a.qkv + i); }
   __device__ __forceinline__ void part(float* p, float v) const { *p = v; }

@@ -121,6 +121,7 @@ struct MfmaArgs {
   int ks, ktq, kstride;     // set by the launcher: parts, k-tiles per part, floats per block of kpart
   // large batches (mfma_wide.hip)
   const float* inv_in;      // QKV, gate/up: 1/rms per sequence
+  int part_seqs;            // QKV: sequences between its parts in out
   int passes;               // set by the launcher
 };
 // the split scratch a projection needs at up to `batch` sequences (mode 0
@@ -134,7 +135,7 @@ hipError_t launch_mfma_down(const MfmaArgs& a, hipStream_t s, KernelEvents ev = 
 // the layout of wide_operand_offset.
 constexpr int kWideMinBatch = 17;
 constexpr int kWideMaxParts = 4;  // parts of the O and down projections
-constexpr int kWideQkvParts = 2;  // parts of q|k|v: out is [kWideQkvParts][batch][rows]
+constexpr int kWideQkvParts = 2;  // parts of q|k|v: out is [kWideQkvParts][part_seqs][rows]
 // floats of kpart the O or down projection needs for up to `batch` sequences
 size_t wide_part_floats(int ns, int kt, int rh, int rows, int batch);
 // op, inv: room for the QKV operand and 1/rms(x)
@@ -143,8 +144,9 @@ hipError_t launch_wide_qkv(const MfmaArgs& a, uint16_t* op, float* inv, hipStrea
 hipError_t launch_wide_oproj(const MfmaArgs& a, float* inv, hipStream_t s, KernelEvents ev = {});
 hipError_t launch_wide_gate_up(const MfmaArgs& a, hipStream_t s, KernelEvents ev = {});
 hipError_t launch_wide_down(const MfmaArgs& a, hipStream_t s, KernelEvents ev = {});
-// dst[n] = the two parts of q|k|v, `part` floats apart, added
-hipError_t launch_wide_qkv_sum(const float* parts, size_t part, size_t n, float* dst, hipStream_t s);
+// dst[batch, rows] = q|k|v, where split[b] is set its two parts, `part` floats apart, added
+hipError_t launch_wide_qkv_sum(const float* parts, size_t part, const int* split, int rows, int batch, float* dst,
+                               hipStream_t s);
 // the MFMA-tiled copy of a row-major [rows, din] matrix with row stride ld,
 // in stripes of rh rows; with `up` set, stripes of rh / 2 rows of src (gate)
 // and the rh / 2 matching rows of up
@@ -174,6 +176,8 @@ struct AttnArgs {
   PosArray order;          // grid z -> sequence: the longest first, so the shortest blocks go last
   float* dbg_qk;           // test hook, null in normal steps: q and k after RoPE (fp32)
                            // [batch, (H + H_kv) d], q heads first
+  int* qkv_split;          // layers that take such batches (else null): per sequence, whether the
+                           // last step's q|k|v came in two parts (for the test hook)
   size_t qkv_part;         // large batches: floats from q|k|v to its second part, to be added (else 0)
   int o_wide;              // large batches: o_operand in the layout of wide_operand_offset
   int direct;              // one split: write o and o_operand instead of a record to be combined

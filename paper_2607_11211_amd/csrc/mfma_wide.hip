@@ -215,7 +215,7 @@ __global__ __launch_bounds__(kWT) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           float v = col(c, b, n);
           if (MODE == WMode::kQkv) v *= a.inv_in[min(b, nb - 1)];
           if (q < nc * NOUT && b < nb && n < R && row < a.rows)
-            a.out[((size_t)kq * nb + b) * a.rows + row] = v;
+            a.out[((size_t)kq * a.part_seqs + b) * a.rows + row] = v;
         }
       }
       if (c0 + CH < N || a.passes > 1) __syncthreads();
@@ -334,11 +334,14 @@ __global__ __launch_bounds__(256) void wide_down_sum_kernel(const float* __restr
   reinterpret_cast<uint2*>(y)[i] = make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
 }
 
-// dst = src + the second part (the test hook's view of the QKV parts)
-__global__ __launch_bounds__(256) void wide_pair_sum_kernel(const float* __restrict__ src, size_t part, size_t n,
+// the test hook's view of q|k|v, one block row per sequence
+__global__ __launch_bounds__(256) void wide_pair_sum_kernel(const float* __restrict__ src, size_t part,
+                                                            const int* __restrict__ split, int rows,
                                                             float* __restrict__ dst) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) dst[i] = src[i] + src[part + i];
+  const int c = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
+  if (c >= rows) return;
+  const size_t i = (size_t)b * rows + c;
+  dst[i] = split[b] ? src[i] + src[part + i] : src[i];
 }
 
 // stripes whose sums a lane holds at once
@@ -429,6 +432,7 @@ size_t wide_part_floats(int ns, int kt, int rh, int rows, int batch) {
 
 hipError_t launch_wide_qkv(const MfmaArgs& a_in, uint16_t* op, float* inv, hipStream_t s, KernelEvents ev) {
   MfmaArgs a = a_in;
+  if (a.part_seqs < a.batch) return hipErrorInvalidValue;
   hipLaunchKernelGGL(wide_prep_kernel, dim3(a.batch), dim3(kPrepThreads), 0, s, a.x_bf16, a.gamma, a.din, a.eps,
                      a.nbtc, op, inv);
   const hipError_t e = hipGetLastError();
@@ -443,6 +447,7 @@ hipError_t launch_wide_oproj(const MfmaArgs& a_in, float* inv, hipStream_t s, Ke
   const int parts = wide_geom(WMode::kPart, a.ns, a.kt, a.rh, a.batch).ks;
   if (!a.kpart || a.kpart_cap < (size_t)parts * a.batch * a.rows || a.rows > 8192) return hipErrorInvalidValue;
   a.out = a.kpart;
+  a.part_seqs = a.batch;
   const hipError_t e = launch_mode<WMode::kPart>(a, s, ev);
   if (e != hipSuccess) return e;
   const int threads = (a.rows / 8 + kWave - 1) / kWave * kWave;
@@ -460,6 +465,7 @@ hipError_t launch_wide_down(const MfmaArgs& a_in, hipStream_t s, KernelEvents ev
   const int parts = wide_geom(WMode::kPart, a.ns, a.kt, a.rh, a.batch).ks;
   if (!a.kpart || a.kpart_cap < (size_t)parts * a.batch * a.rows) return hipErrorInvalidValue;
   a.out = a.kpart;
+  a.part_seqs = a.batch;
   const hipError_t e = launch_mode<WMode::kPart>(a, s, ev);
   if (e != hipSuccess) return e;
   const int n4 = a.batch * a.rows / 4;
@@ -468,9 +474,10 @@ hipError_t launch_wide_down(const MfmaArgs& a_in, hipStream_t s, KernelEvents ev
   return hipGetLastError();
 }
 
-hipError_t launch_wide_qkv_sum(const float* parts, size_t part, size_t n, float* dst, hipStream_t s) {
-  hipLaunchKernelGGL(wide_pair_sum_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, parts, part, n, dst);
-  return hipGetLastError();
+hipError_t launch_wide_qkv_sum(const float* parts, size_t part, const int* split, int rows, int batch, float* dst,
+                               hipStream_t s) {
+  return ext_launch(wide_pair_sum_kernel, dim3((rows + 255) / 256, batch), dim3(256), 0, s, KernelEvents{}, parts, part,
+                    split, rows, dst);
 }
 
 }  // namespace fasttps

@@ -115,3 +115,55 @@ def test_wide_replays_equal_eager():
     del g
     W.free()
     lay.destroy()
+
+
+def test_qkv_hook_after_other_batches_and_replays():
+    """FASTTPS_DBG_QKV gives each row as the last step that held it left it:
+    steps of 40 and 20 sequences (two parts), of 3 and 1 (whole sums), and a
+    replayed step of 3 after an eager one of 40, read at 40 sequences."""
+    import torch
+    from paper_2607_11211_amd import layer as L
+    cfg = _cfg("w_hook", 109, 40, 512, 32, 8, 128, 7200, 60)
+    inp = inputs.make_layer_inputs(cfg)
+    lay = L.Layer(cfg)
+    W = lay.pack({k: L.to_device(v) for k, v in inp.weights.items()})
+    kc, vc = L.to_device(inp.k_cache), L.to_device(inp.v_cache)
+    xs = {n: L.to_device(inputs.make_x(cfg, seed=400 + n)) for n in (40, 20, 3, 1)}
+    y = torch.empty_like(xs[40])
+
+    def step(n, stream=None):
+        lay.step(W, xs[n][:n], inp.pos[:n], kc, vc, y[:n], stream)
+
+    def read(n):
+        t = torch.empty(n, cfg.qkv_rows, dtype=torch.float32, device="cuda")
+        lay.debug_read(L.DBG_QKV, n, t)
+        torch.cuda.synchronize()
+        return t.cpu().numpy()
+
+    want = {}
+    for n in (40, 20, 3, 1):  # each step's own rows
+        step(n)
+        want[n] = read(n)
+    rows = want[40].copy()
+    step(40)
+    for n in (20, 3, 1, 20):
+        step(n)
+        rows[:n] = want[n]
+        assert np.array_equal(read(40), rows), f"after a step of {n}"
+
+    g = torch.cuda.CUDAGraph()
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        with torch.cuda.graph(g, stream=s):
+            step(3, s)
+    torch.cuda.current_stream().wait_stream(s)
+    rows[:] = want[40]
+    rows[:3] = want[3]
+    for rep in range(3):
+        step(40)
+        g.replay()
+        assert np.array_equal(read(40), rows), f"replay {rep}"
+    del g
+    W.free()
+    lay.destroy()
