@@ -352,9 +352,10 @@ FASTTPS_API int fasttps_validate_step(const fasttps_config* cfg, const void* x, 
                                   a kernel a step does not launch reads 0 (the combine at
                                   batch 1, where the O projection merges the splits and is
                                   timed as kernel 3, and where each sequence has one split);
-                                  beyond 16 sequences the small kernels that prepare the QKV
-                                  operand and add the parts of the O and down projections
-                                  are not timed */
+                                  where the large-batch projections run (up to 64 sequences,
+                                  weights read once), kernels 0, 3 and 5 are two launches
+                                  each (the QKV operand and the sums of the parts are small
+                                  kernels of their own) and read the sum of both */
 FASTTPS_API int fasttps_profile_begin(fasttps_layer* layer, int32_t max_steps);
 FASTTPS_API int fasttps_profile_end(fasttps_layer* layer, float* ms, int32_t max_steps, int32_t* n_steps);
 FASTTPS_API const char* fasttps_kernel_name(int32_t k);

@@ -234,8 +234,11 @@ struct fasttps_layer {
   void* uf_arena = nullptr;
   UnfusedArgs uf{};
   // per-kernel timing (measurement hook)
-  std::vector<hipEvent_t> prof_events;  // [cap][kernel][start, stop]
-  std::vector<uint8_t> prof_used;       // [cap][kernel]: launched with its events
+  // per-kernel events [cap][kernel][prof_launches][start, stop]; the O
+  // projection of mfma_wide.hip, say, is two launches
+  std::vector<hipEvent_t> prof_events;
+  std::vector<uint8_t> prof_used;  // [cap][kernel]: launches made with their events
+  int prof_launches = 1;
   int prof_cap = 0;
   int prof_n = 0;
 };
@@ -515,7 +518,8 @@ int fasttps_profile_begin(fasttps_layer* l, int32_t max_steps) {
   if (!layer_ok(l)) return fail(FASTTPS_ERR_BAD_HANDLE, "bad layer handle");
   if (max_steps < 1 || max_steps > (1 << 16)) return fail(FASTTPS_ERR_INVALID_ARG, "max_steps out of range");
   release_events(l);
-  l->prof_events.resize((size_t)max_steps * FASTTPS_NUM_KERNELS * 2, nullptr);
+  l->prof_launches = l->qkv_split ? 2 : 1;
+  l->prof_events.resize((size_t)max_steps * FASTTPS_NUM_KERNELS * l->prof_launches * 2, nullptr);
   l->prof_used.assign((size_t)max_steps * FASTTPS_NUM_KERNELS, 0);
   for (auto& ev : l->prof_events) {
     hipError_t e = hipEventCreate(&ev);
@@ -537,18 +541,24 @@ int fasttps_profile_end(fasttps_layer* l, float* ms, int32_t max_steps, int32_t*
   const int n = std::min(l->prof_n, (int)max_steps);
   *n_steps = n;
   hipError_t e = hipSuccess;
-  // the last launched kernel of the last recorded step
+  const size_t nl = l->prof_launches;
+  // the last launch of the last recorded step
   if (l->prof_n > 0) {
     const size_t st = (size_t)(l->prof_n - 1) * FASTTPS_NUM_KERNELS;
     int kl = FASTTPS_NUM_KERNELS - 1;
     while (kl > 0 && !l->prof_used[st + kl]) --kl;
-    e = hipEventSynchronize(l->prof_events[(st + kl) * 2 + 1]);
+    e = hipEventSynchronize(l->prof_events[((st + kl) * nl + std::max<int>(l->prof_used[st + kl], 1) - 1) * 2 + 1]);
   }
   for (int i = 0; i < n && e == hipSuccess; ++i)
     for (int k = 0; k < FASTTPS_NUM_KERNELS && e == hipSuccess; ++k) {
       const size_t j = (size_t)i * FASTTPS_NUM_KERNELS + k;
       ms[j] = 0.f;
-      if (l->prof_used[j]) e = hipEventElapsedTime(&ms[j], l->prof_events[2 * j], l->prof_events[2 * j + 1]);
+      for (int q = 0; q < l->prof_used[j] && e == hipSuccess; ++q) {
+        const size_t i2 = (j * nl + q) * 2;
+        float t = 0.f;
+        e = hipEventElapsedTime(&t, l->prof_events[i2], l->prof_events[i2 + 1]);
+        ms[j] += t;
+      }
     }
   release_events(l);
   if (e != hipSuccess) return hip_fail(e, "kernel timing");
@@ -879,18 +889,22 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
   if (dev != l->device) return fail(FASTTPS_ERR_INVALID_ARG, "current device %d is not the layer's device %d", dev, l->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const uint16_t* xb = static_cast<const uint16_t*>(x);
-  KernelEvents ev[FASTTPS_NUM_KERNELS];
+  KernelEvents ev[FASTTPS_NUM_KERNELS], ev2[FASTTPS_NUM_KERNELS];  // ev2: a kernel's second launch
   const bool timed = !S.noalloc && l->prof_n < l->prof_cap;
   const bool debug = !S.noalloc && l->debug;
   if (timed) {
     for (int k = 0; k < FASTTPS_NUM_KERNELS; ++k) {
-      const size_t i = ((size_t)l->prof_n * FASTTPS_NUM_KERNELS + k) * 2;
+      const size_t i = ((size_t)l->prof_n * FASTTPS_NUM_KERNELS + k) * l->prof_launches * 2;
       ev[k].start = l->prof_events[i];
       ev[k].stop = l->prof_events[i + 1];
+      if (l->prof_launches > 1) {
+        ev2[k].start = l->prof_events[i + 2];
+        ev2[k].stop = l->prof_events[i + 3];
+      }
     }
   }
-  auto used = [&](int k) {
-    if (timed) l->prof_used[(size_t)l->prof_n * FASTTPS_NUM_KERNELS + k] = 1;
+  auto used = [&](int k, int launches = 1) {
+    if (timed) l->prof_used[(size_t)l->prof_n * FASTTPS_NUM_KERNELS + k] = (uint8_t)launches;
   };
 
   // the vector path's arguments (also the fused kernel's phases)
@@ -1017,14 +1031,15 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
     if (wide) {
       // the QKV operand and 1/rms(x) in buffers the O projection fills later
       // (the gate/up operand has the same inputs)
-      if ((e = launch_wide_qkv(m, l->op_gu, l->ssq_h1, s, ev[0])) != hipSuccess) return hip_fail(e, "qkv launch");
+      if ((e = launch_wide_qkv(m, l->op_gu, l->ssq_h1, s, ev[0], ev2[0])) != hipSuccess)
+        return hip_fail(e, "qkv launch");
     } else if ((e = launch_mfma_qkv(m, s, ev[0])) != hipSuccess) {
       return hip_fail(e, "qkv launch");
     }
   } else {
     if ((e = launch_rmsnorm_qkv(qa, s, ev[0])) != hipSuccess) return hip_fail(e, "qkv launch");
   }
-  used(0);
+  used(0, wide ? 2 : 1);
 
   // one sequence on the vector path: the O projection merges the splits in
   // its prologue, one launch fewer (Phi-3 layer on MI355X, HIP graph: 60.1 ->
@@ -1052,7 +1067,7 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
     m.out = S.h1;
     m.a_out = l->op_gu;
     m.ssq_out = l->ssq_h1;
-    e = wide ? launch_wide_oproj(m, l->ssq_h1, s, ev[3]) : launch_mfma_oproj(m, s, ev[3]);
+    e = wide ? launch_wide_oproj(m, l->ssq_h1, s, ev[3], ev2[3]) : launch_mfma_oproj(m, s, ev[3]);
     if (e != hipSuccess) return hip_fail(e, "o-proj launch");
     m = mfma_args(lt.gu, w->t_gu, c.intermediate, (int)D);
     m.a_in = l->op_gu;
@@ -1067,7 +1082,7 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
     m.a_in = l->op_down;
     m.res_f32 = S.h1;
     m.out_bf16 = static_cast<uint16_t*>(y);
-    e = wide ? launch_wide_down(m, s, ev[5]) : launch_mfma_down(m, s, ev[5]);
+    e = wide ? launch_wide_down(m, s, ev[5], ev2[5]) : launch_mfma_down(m, s, ev[5]);
     if (e != hipSuccess) return hip_fail(e, "mlp down launch");
   } else {
     if (merge_in_o) {
@@ -1097,9 +1112,9 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
       if ((e = launch_down_residual(da, s, ev[5])) != hipSuccess) return hip_fail(e, "mlp down launch");
     }
   }
-  used(3);
+  used(3, wide ? 2 : 1);
   used(4);
-  used(5);
+  used(5, wide ? 2 : 1);
   if (timed) ++l->prof_n;
   if (debug) l->dbg_written = kDbgQk | (mfma ? 0 : kDbgNorm);
   return FASTTPS_OK;

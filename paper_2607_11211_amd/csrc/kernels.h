@@ -138,12 +138,15 @@ constexpr int kWideMaxParts = 4;  // parts of the O and down projections
 constexpr int kWideQkvParts = 2;  // parts of q|k|v: out is [kWideQkvParts][part_seqs][rows]
 // floats of kpart the O or down projection needs for up to `batch` sequences
 size_t wide_part_floats(int ns, int kt, int rh, int rows, int batch);
-// op, inv: room for the QKV operand and 1/rms(x)
-hipError_t launch_wide_qkv(const MfmaArgs& a, uint16_t* op, float* inv, hipStream_t s, KernelEvents ev = {});
+// op, inv: room for the QKV operand and 1/rms(x); ev, ev2: the events of the
+// first and the second launch (the operand and the projection, or the
+// projection and the sum of its parts)
+hipError_t launch_wide_qkv(const MfmaArgs& a, uint16_t* op, float* inv, hipStream_t s, KernelEvents ev = {},
+                           KernelEvents ev2 = {});
 // inv: RMSNorm2's factor per sequence
-hipError_t launch_wide_oproj(const MfmaArgs& a, float* inv, hipStream_t s, KernelEvents ev = {});
+hipError_t launch_wide_oproj(const MfmaArgs& a, float* inv, hipStream_t s, KernelEvents ev = {}, KernelEvents ev2 = {});
 hipError_t launch_wide_gate_up(const MfmaArgs& a, hipStream_t s, KernelEvents ev = {});
-hipError_t launch_wide_down(const MfmaArgs& a, hipStream_t s, KernelEvents ev = {});
+hipError_t launch_wide_down(const MfmaArgs& a, hipStream_t s, KernelEvents ev = {}, KernelEvents ev2 = {});
 // dst[batch, rows] = q|k|v, where split[b] is set its two parts, `part` floats apart, added
 hipError_t launch_wide_qkv_sum(const float* parts, size_t part, const int* split, int rows, int batch, float* dst,
                                hipStream_t s);

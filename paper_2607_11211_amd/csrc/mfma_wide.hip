@@ -430,19 +430,19 @@ size_t wide_part_floats(int ns, int kt, int rh, int rows, int batch) {
   return most;
 }
 
-hipError_t launch_wide_qkv(const MfmaArgs& a_in, uint16_t* op, float* inv, hipStream_t s, KernelEvents ev) {
+hipError_t launch_wide_qkv(const MfmaArgs& a_in, uint16_t* op, float* inv, hipStream_t s, KernelEvents ev,
+                           KernelEvents ev2) {
   MfmaArgs a = a_in;
   if (a.part_seqs < a.batch) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(wide_prep_kernel, dim3(a.batch), dim3(kPrepThreads), 0, s, a.x_bf16, a.gamma, a.din, a.eps,
-                     a.nbtc, op, inv);
-  const hipError_t e = hipGetLastError();
+  const hipError_t e = ext_launch(wide_prep_kernel, dim3(a.batch), dim3(kPrepThreads), 0, s, ev, a.x_bf16, a.gamma,
+                                  a.din, a.eps, a.nbtc, op, inv);
   if (e != hipSuccess) return e;
   a.a_in = op;
   a.inv_in = inv;
-  return launch_mode<WMode::kQkv>(a, s, ev);
+  return launch_mode<WMode::kQkv>(a, s, ev2);
 }
 
-hipError_t launch_wide_oproj(const MfmaArgs& a_in, float* inv, hipStream_t s, KernelEvents ev) {
+hipError_t launch_wide_oproj(const MfmaArgs& a_in, float* inv, hipStream_t s, KernelEvents ev, KernelEvents ev2) {
   MfmaArgs a = a_in;
   const int parts = wide_geom(WMode::kPart, a.ns, a.kt, a.rh, a.batch).ks;
   if (!a.kpart || a.kpart_cap < (size_t)parts * a.batch * a.rows || a.rows > 8192) return hipErrorInvalidValue;
@@ -451,16 +451,15 @@ hipError_t launch_wide_oproj(const MfmaArgs& a_in, float* inv, hipStream_t s, Ke
   const hipError_t e = launch_mode<WMode::kPart>(a, s, ev);
   if (e != hipSuccess) return e;
   const int threads = (a.rows / 8 + kWave - 1) / kWave * kWave;
-  hipLaunchKernelGGL(wide_oproj_sum_kernel, dim3(a.batch), dim3(threads), 0, s, (const float*)a.kpart, parts, a.batch,
-                     a.x_bf16, a.gamma, a.rows, a.eps, a_in.out, a.a_out, a.a_out_nbtc, inv);
-  return hipGetLastError();
+  return ext_launch(wide_oproj_sum_kernel, dim3(a.batch), dim3(threads), 0, s, ev2, (const float*)a.kpart, parts,
+                    a.batch, a.x_bf16, a.gamma, a.rows, a.eps, a_in.out, a.a_out, a.a_out_nbtc, inv);
 }
 
 hipError_t launch_wide_gate_up(const MfmaArgs& a, hipStream_t s, KernelEvents ev) {
   return launch_mode<WMode::kGateUp>(a, s, ev);
 }
 
-hipError_t launch_wide_down(const MfmaArgs& a_in, hipStream_t s, KernelEvents ev) {
+hipError_t launch_wide_down(const MfmaArgs& a_in, hipStream_t s, KernelEvents ev, KernelEvents ev2) {
   MfmaArgs a = a_in;
   const int parts = wide_geom(WMode::kPart, a.ns, a.kt, a.rh, a.batch).ks;
   if (!a.kpart || a.kpart_cap < (size_t)parts * a.batch * a.rows) return hipErrorInvalidValue;
@@ -469,9 +468,8 @@ hipError_t launch_wide_down(const MfmaArgs& a_in, hipStream_t s, KernelEvents ev
   const hipError_t e = launch_mode<WMode::kPart>(a, s, ev);
   if (e != hipSuccess) return e;
   const int n4 = a.batch * a.rows / 4;
-  hipLaunchKernelGGL(wide_down_sum_kernel, dim3((n4 + 255) / 256), dim3(256), 0, s, (const float*)a.kpart, parts, n4,
-                     a.res_f32, a.out_bf16);
-  return hipGetLastError();
+  return ext_launch(wide_down_sum_kernel, dim3((n4 + 255) / 256), dim3(256), 0, s, ev2, (const float*)a.kpart, parts,
+                    n4, a.res_f32, a.out_bf16);
 }
 
 hipError_t launch_wide_qkv_sum(const float* parts, size_t part, const int* split, int rows, int batch, float* dst,

@@ -167,3 +167,47 @@ def test_qkv_hook_after_other_batches_and_replays():
     del g
     W.free()
     lay.destroy()
+
+
+def test_profile_covers_every_launch():
+    """The per-kernel times of a step cover its small kernels too: on a layer
+    where the QKV operand and the sums of the parts are a fifth of the step
+    (83 us on MI355X, 68 of them without those, 86 with them: each launch
+    timed alone takes a little longer), the times add up to the replayed step."""
+    import torch
+    from paper_2607_11211_amd import layer as L
+    cfg = _cfg("w_prof", 110, 64, 8192, 1, 1, 64, 384)
+    inp = inputs.make_layer_inputs(cfg)
+    lay = L.Layer(cfg)
+    W = lay.pack({k: L.to_device(v) for k, v in inp.weights.items()})
+    x = L.to_device(inp.x)
+    kc, vc = L.to_device(inp.k_cache), L.to_device(inp.v_cache)
+    y = torch.empty_like(x)
+    for _ in range(3):
+        lay.step(W, x, inp.pos, kc, vc, y)
+    torch.cuda.synchronize()
+    lay.profile_begin(12)
+    for _ in range(12):
+        lay.step(W, x, inp.pos, kc, vc, y)
+    per_kernel = np.median(lay.profile_end(12), axis=0) * 1e3
+    g = torch.cuda.CUDAGraph()
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        with torch.cuda.graph(g, stream=s):
+            for _ in range(10):
+                lay.step(W, x, inp.pos, kc, vc, y, s)
+    torch.cuda.current_stream().wait_stream(s)
+    steps = []
+    for _ in range(4):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        g.replay()
+        b.record()
+        torch.cuda.synchronize()
+        steps.append(a.elapsed_time(b) * 1e3 / 10)
+    log(f"per kernel us {per_kernel.round(2)}, step {min(steps):.2f}")
+    assert 0.92 * min(steps) <= per_kernel.sum() <= 1.5 * min(steps)
+    del g
+    W.free()
+    lay.destroy()
