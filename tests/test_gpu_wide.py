@@ -3,7 +3,9 @@ against the fp64 oracle, through the C ABI (MI355X), to the bars of the other
 projection paths: sequence tiles of 16 filled and ragged, one stripe per block
 up to several passes of stripes, k-tiles fewer than the block's waves, padded
 stripes and k-tiles, parts, and steps below and above the 16-sequence
-limit on one handle."""
+limit on one handle; the attention kernels as these steps run them (q|k|v in
+two parts), over bf16 and 8-bit caches; and what the test and measurement
+hooks read after such steps."""
 import numpy as np
 import pytest
 
@@ -57,6 +59,91 @@ def test_wide_matches_oracle(cfg):
     r = ref.decode_layer_cfg(cfg, inp.x, inp.pos, inp.k_cache, inp.v_cache, inp.weights)
     gpu = run_gpu(cfg, inp)
     full_check(cfg, inp, gpu, r)
+
+
+def _long(name, index, hidden, heads, kv, d, inter, pos):
+    cfg = LayerConfig(name=name, index=index, batch=len(pos), hidden=hidden, n_heads=heads, n_kv_heads=kv, head_dim=d,
+                      intermediate=inter, rope_base=10000.0, max_seq=max(pos) + 2, pos=tuple(pos))
+    # past the line of the dispatch: 25 MB read again by the kernels of 16 sequences
+    weights = 2 * hidden * ((2 * heads + 2 * kv) * d + 3 * inter)
+    assert weights * ((cfg.batch - 1) // 16) >= 25 << 20, name
+    return cfg
+
+
+def _spread(n, lo, hi):
+    return tuple(lo + (i * 37) % (hi - lo + 1) for i in range(n))
+
+
+# the attention kernels as these steps run them: q|k|v in two parts, o into the operand of 16-sequence tiles
+ATTENTION = [
+    # matrix cores: groups of two and four, several splits and one
+    _long("w_g2_d128", 150, 512, 8, 4, 128, 8704, _spread(19, 0, 400)),
+    _long("w_g2_d96", 151, 512, 4, 2, 96, 8704, _spread(17, 60, 300)),
+    _long("w_g2_d64_128", 152, 512, 4, 2, 64, 8704, _spread(18, 70, 128)),
+    _long("w_g4_one", 153, 512, 64, 16, 128, 8000, _spread(17, 1, 1000)),
+    # vector kernel: groups of two at d = 64
+    _long("w_g2_d64_vec", 154, 512, 4, 2, 64, 8704, _spread(17, 100, 500)),
+    # one head: tiles exchanged through LDS (8 or more per split), in two splits and in one
+    _long("w_xch_d128", 155, 512, 16, 16, 128, 8000, _spread(17, 1060, 1100)),
+    _long("w_xch_d96_one", 156, 512, 16, 16, 96, 8704, _spread(17, 600, 1000)),
+    _long("w_xch_d64", 157, 512, 16, 16, 64, 8704, _spread(17, 1100, 1200)),
+    # more than 32 splits: the block-wide combine
+    _long("w_combine", 158, 512, 2, 1, 128, 8704, (6000,) + _spread(16, 0, 60)),
+    _long("w_combine_d96", 159, 512, 1, 1, 96, 8704, (3000,) + _spread(32, 0, 60)),
+]
+
+
+@pytest.mark.parametrize("cfg", ATTENTION, ids=lambda c: c.name)
+def test_attention_of_large_batches(cfg):
+    log(f"start {cfg.name}")
+    inp = inputs.make_layer_inputs(cfg)
+    r = ref.decode_layer_cfg(cfg, inp.x, inp.pos, inp.k_cache, inp.v_cache, inp.weights)
+    full_check(cfg, inp, run_gpu(cfg, inp), r)
+
+
+# the same over 8-bit caches, on both sides of the matrix cores' lines (2^18 rows; 17 * 2^15 for
+# groups of two at d = 64)
+KV8 = [
+    _long("w8_g1_d128", 160, 512, 4, 4, 128, 8704, _spread(20, 0, 300)),
+    _long("w8_g1_d96", 161, 512, 4, 4, 96, 8704, _spread(33, 0, 200)),
+    _long("w8_g1_d64", 162, 512, 4, 4, 64, 8704, _spread(17, 5, 300)),
+    _long("w8_g2_d128", 163, 512, 4, 2, 128, 8704, _spread(17, 5, 300)),
+    _long("w8_g2_d96", 164, 512, 4, 2, 96, 8704, _spread(18, 0, 200)),
+    _long("w8_g2_d64", 165, 512, 4, 2, 64, 8704, _spread(18, 0, 200)),
+    _long("w8_g4_d64", 166, 512, 8, 2, 64, 8704, _spread(18, 0, 300)),
+    _long("w8_g4_d96", 167, 512, 4, 1, 96, 8704, _spread(17, 0, 300)),
+    _long("w8_g4_d128", 168, 512, 8, 2, 128, 8704, _spread(33, 0, 300)),
+    _long("w8_g1_d128_long", 169, 512, 16, 16, 128, 8000, _spread(17, 965, 1005)),
+    _long("w8_g1_d96_long", 170, 512, 16, 16, 96, 8704, _spread(17, 1025, 1060)),
+    _long("w8_g2_d128_long", 171, 256, 32, 16, 128, 14000, _spread(17, 965, 1100)),
+    _long("w8_g2_d96_long", 172, 256, 32, 16, 96, 15000, _spread(17, 965, 1005)),
+    _long("w8_g2_d64_long", 173, 256, 64, 32, 64, 7000, _spread(33, 530, 560)),
+]
+
+
+@pytest.mark.parametrize("fmt", inputs.KV8_FORMATS)
+@pytest.mark.parametrize("cfg", KV8, ids=lambda c: c.name)
+def test_kv8_attention_of_large_batches(cfg, fmt):
+    from test_gpu_kv8 import run_case
+    log(f"start {cfg.name} {fmt}")
+    run_case(cfg, inputs.make_layer_inputs(cfg), fmt)
+
+
+@pytest.mark.parametrize("cfg", [c for c in ATTENTION if c.name in ("w_g2_d128", "w_g2_d64_vec", "w_xch_d96_one")],
+                         ids=lambda c: c.name)
+def test_study_switch_of_large_batches(cfg):
+    """The accuracy study's bf16 weights (vector kernel) with q|k|v in two parts."""
+    from gpu_harness import check_y
+    from paper_2607_11211_amd import layer as L
+    log(f"start {cfg.name} p_bf16")
+    inp = inputs.make_layer_inputs(cfg)
+    r = ref.decode_layer_cfg(cfg, inp.x, inp.pos, inp.k_cache, inp.v_cache, inp.weights)
+    lay = L.Layer(cfg)
+    lay.set_attention_p_bf16(True)
+    got = run_gpu(cfg, inp, layer=lay, keep=True)
+    check_y(got, r)
+    got["_weights"].free()
+    lay.destroy()
 
 
 def test_batches_around_the_limit_on_one_handle():
