@@ -745,56 +745,6 @@ int fasttps_validate_step(const fasttps_config* cfg, const void* x, const int32_
 
 namespace {
 
-// The attention of a step: which kernel (attention_on_mfma), and into how many
-// splits the tiles (64 cached positions, 128 on the matrix cores) of [0, pos)
-// of every (sequence, kv head) are dealt, of about split_len positions each,
-// so that about `target` blocks carry the work (the new entry at pos comes
-// from registers, so it adds no tile of its own).
-struct AttnPlan {
-  bool mfma;
-  int nsplit;
-};
-AttnPlan attention_plan(const fasttps_layer* l, const int32_t* pos, int32_t batch, int maxp, int kvf) {
-  const fasttps_config& c = l->cfg;
-  const int maxn = std::max(maxp, 1);
-  long total = 0;
-  int minp = maxp;
-  for (int b = 0; b < batch; ++b) {
-    total += pos[b];
-    minp = std::min(minp, (int)pos[b]);
-  }
-  AttnPlan p;
-  p.mfma = attention_on_mfma(
-      {c.n_heads / c.n_kv_heads, c.head_dim, kvf, l->p_bf16, batch, maxp, total * c.n_kv_heads});
-  const int tile = p.mfma ? kAttnMfmaTile : kAttnTile;
-  // Ragged batches on the vector kernel: two or four times the blocks, so that
-  // the short sequences' splits do not end early, from 1024 and 2048 positions
-  // a block up; below, the blocks' prologues and merges and the combine cost
-  // more (and on the matrix cores at any length). MI355X, layer step with 512 /
-  // 1024 / 2048 blocks: Phi-3, 4 sequences of 65-2500 entries (320 a block)
-  // 65.7 / 66.1 / 67.5 us, 3 of 500-8000 (800) 84.1 / 88.0 / 88.0, 16 of
-  // 65-2500 (1280) 101.0 / 101.6 / 108.2, 4 of 500-8000 (1060) 90.3 / 87.8 /
-  // 93.1, 16 of 500-8000 (4250) 186.8 / 185.8 / 184.7; matrix cores, d 128,
-  // groups of four, 4 of 500-8000 53.8 / 53.7 / 57.1
-  const long per_block = total * c.n_kv_heads / kTargetAttnBlocks;
-  const int ragged = minp == maxp || p.mfma || per_block < 1024 ? 1 : per_block < 2048 ? 2 : kRaggedAttnFactor;
-  const long target = batch == 1 ? kTargetAttnBlocksOne : ragged * (long)kTargetAttnBlocks;
-  int split_len = round_up((int)std::min<long>((total * c.n_kv_heads + target - 1) / target, maxn), tile);
-  split_len = std::max(split_len, round_up(ceil_div(maxn, l->nsplit_cap), tile));
-  p.nsplit = ceil_div(maxn, split_len);
-  // Where the (sequence, KV head) pairs alone fill the chip and the contexts
-  // are short, one split each: the attention then writes the finished o and
-  // the combine launch (4 us and its boundary) is gone. MI355X, layer step,
-  // several splits against one: Phi-3, 256 pairs, 300 entries 62.4 against
-  // 60.3 us, 20-400 ragged 65.5 / 59.6, 1000 70.8 / 69.0, 4000 118.1 / 120.4;
-  // 512 pairs, 100-2000 ragged 100.1 / 94.5, FP8 79.1 / 77.0 (256 pairs: 67.8
-  // / 70.4), 500-4096 ragged 128.4 / 129.2; Llama3-8B, 256 pairs, 20-400
-  // ragged 100.1 / 93.3, 512 pairs, 500-4096 ragged 214.7 / 220.6
-  const int pairs = batch * c.n_kv_heads;
-  if (pairs >= kOneSplitPairs && maxn <= (pairs < 2 * kOneSplitPairs ? 1024 : 2048)) p.nsplit = 1;
-  return p;
-}
-
 // Where a step keeps its fp32 intermediates: the layer handle's scratch, or
 // (the allocation-free step) the static array, with the split partials laid
 // out for exactly the step's nsplit splits.
@@ -827,6 +777,64 @@ size_t noalloc_layout(const fasttps_config& c, int batch, int nsplit, float* bas
                        reinterpret_cast<float*>(p + offs[4]), nsplit, true};
   }
   return total;
+}
+
+// The attention of a step: which kernel (attention_on_mfma), and into how many
+// splits the tiles (64 cached positions, 128 on the matrix cores) of [0, pos)
+// of every (sequence, kv head) are dealt, of about split_len positions each,
+// so that about `target` blocks carry the work (the new entry at pos comes
+// from registers, so it adds no tile of its own).
+struct AttnPlan {
+  bool mfma;
+  int nsplit;
+};
+AttnPlan attention_plan(const fasttps_layer* l, const int32_t* pos, int32_t batch, int maxp, int kvf) {
+  const fasttps_config& c = l->cfg;
+  const int maxn = std::max(maxp, 1);
+  long total = 0;
+  int minp = maxp;
+  for (int b = 0; b < batch; ++b) {
+    total += pos[b];
+    minp = std::min(minp, (int)pos[b]);
+  }
+  const AttnShape shape{c.n_heads / c.n_kv_heads, c.head_dim, kvf, l->p_bf16, batch, maxp, total * c.n_kv_heads};
+  auto plan = [&](bool mfma) {
+    const int tile = mfma ? kAttnMfmaTile : kAttnTile;
+    // Ragged batches on the vector kernel: two or four times the blocks, so that
+    // the short sequences' splits do not end early, from 1024 and 2048 positions
+    // a block up; below, the blocks' prologues and merges and the combine cost
+    // more (and on the matrix cores at any length). MI355X, layer step with 512 /
+    // 1024 / 2048 blocks: Phi-3, 4 sequences of 65-2500 entries (320 a block)
+    // 65.7 / 66.1 / 67.5 us, 3 of 500-8000 (800) 84.1 / 88.0 / 88.0, 16 of
+    // 65-2500 (1280) 101.0 / 101.6 / 108.2, 4 of 500-8000 (1060) 90.3 / 87.8 /
+    // 93.1, 16 of 500-8000 (4250) 186.8 / 185.8 / 184.7; matrix cores, d 128,
+    // groups of four, 4 of 500-8000 53.8 / 53.7 / 57.1
+    const long per_block = total * c.n_kv_heads / kTargetAttnBlocks;
+    const int ragged = minp == maxp || mfma || per_block < 1024 ? 1 : per_block < 2048 ? 2 : kRaggedAttnFactor;
+    const long target = batch == 1 ? kTargetAttnBlocksOne : ragged * (long)kTargetAttnBlocks;
+    int split_len = round_up((int)std::min<long>((total * c.n_kv_heads + target - 1) / target, maxn), tile);
+    split_len = std::max(split_len, round_up(ceil_div(maxn, l->nsplit_cap), tile));
+    int nsplit = ceil_div(maxn, split_len);
+    // Where the (sequence, KV head) pairs alone fill the chip and the contexts
+    // are short, one split each: the attention then writes the finished o and
+    // the combine launch (4 us and its boundary) is gone. MI355X, layer step,
+    // several splits against one: Phi-3, 256 pairs, 300 entries 62.4 against
+    // 60.3 us, 20-400 ragged 65.5 / 59.6, 1000 70.8 / 69.0, 4000 118.1 / 120.4;
+    // 512 pairs, 100-2000 ragged 100.1 / 94.5, FP8 79.1 / 77.0 (256 pairs: 67.8
+    // / 70.4), 500-4096 ragged 128.4 / 129.2; Llama3-8B, 256 pairs, 20-400
+    // ragged 100.1 / 93.3, 512 pairs, 500-4096 ragged 214.7 / 220.6
+    const int pairs = batch * c.n_kv_heads;
+    if (pairs >= kOneSplitPairs && maxn <= (pairs < 2 * kOneSplitPairs ? 1024 : 2048)) nsplit = 1;
+    return AttnPlan{mfma, nsplit};
+  };
+  AttnPlan p = plan(attention_on_mfma(shape));
+  // Groups of two that the rule leaves to the vector kernel, where its splits
+  // would not fit the allocation-free step's scratch (both steps run one
+  // plan): the matrix cores' splits are half as many
+  if (!p.mfma && shape.group == 2 && kvf == kKvBf16 && !l->p_bf16 &&
+      noalloc_layout(c, batch, p.nsplit, nullptr, nullptr) > kStaticScratchBytes)
+    p = plan(true);
+  return p;
 }
 
 // The fused step after validation: kvf is the cache format (kKvBf16, or an

@@ -66,6 +66,29 @@ def test_noalloc_matches_step_on_two_calls():
         lay.destroy()
 
 
+def test_noalloc_fits_many_splits_of_groups_of_two():
+    """32 sequences, one of them long, in groups of two at d = 64: in tiles of
+    64 positions the split partials (63 splits, 9.3 MB) would not fit the
+    static array; the step is taken, with the bits of fasttps_decode_step."""
+    from paper_2607_11211_amd import layer as L
+    cfg = LayerConfig(name="na_g2", index=64, batch=32, hidden=128, n_heads=16, n_kv_heads=8, head_dim=64,
+                      intermediate=256, rope_base=10000.0, max_seq=4002, pos=(4000,) + (3,) * 31)
+    inp = inputs.make_layer_inputs(cfg)
+    lay = L.Layer(cfg)
+    lay.set_gemm_path(L.GEMM_VECTOR)
+    W = lay.pack({k: L.to_device(v) for k, v in inp.weights.items()})
+    try:
+        got = _step(L, lay, W, inp, noalloc=True)
+        want = _step(L, lay, W, inp, noalloc=False)
+        assert np.array_equal(got["y"], want["y"]), "y differs from fasttps_decode_step"
+        r = ref.decode_layer_cfg(cfg, inp.x, inp.pos, inp.k_cache, inp.v_cache, inp.weights)
+        check_cache(cfg, inp, got, r)
+        check_y(got, r)
+    finally:
+        W.free()
+        lay.destroy()
+
+
 def test_noalloc_refuses_steps_beyond_its_static_scratch():
     """64 sequences of a hidden-8192, MLP-32768 layer need more than 8 MiB of
     intermediates: refused before any launch, the caches untouched."""
