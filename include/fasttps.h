@@ -130,8 +130,9 @@ FASTTPS_API int fasttps_decode_step(fasttps_layer* layer, const fasttps_weights*
 
 /* fasttps_decode_step for callers that cannot allocate (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
- * same arguments, checks, cache contract and results, computed by the same
- * vector-path kernels (whatever fasttps_set_gemm_path says), with the step's
+ * same arguments, checks, cache contract and results, computed by the kernels
+ * of the vector path (whatever fasttps_set_gemm_path says; the attention of
+ * query groups is on the matrix cores there too), with the step's
  * fp32 intermediates in a static device array of the library (8 MiB per
  * device, held until the process ends) instead of the handle's scratch. The
  * call allocates nothing. Returns FASTTPS_ERR_UNSUPPORTED, before any

@@ -33,9 +33,11 @@
 // over an INT8 cache 96.6 -> 52.2 (5.4 TB/s). K by plain loads: with the
 // non-temporal policy 71 instead of 63 us, by 16 instead of 8 bytes a lane 63 -> 57 us
 // (INT8); V non-temporal: 84 us, plain 94 (4 x 32768).
-// Non-finite cache entries give what the vector kernel gives: the mid and lo
-// levels' contributions are dropped where they are not finite (0 * inf), the
-// hi level alone then carries the infinity.
+// Non-finite cache entries: the mid and lo levels' contributions are dropped
+// where they are not finite (0 * inf), the hi level alone then carries the
+// infinity, as in the vector kernel's products. A score of -inf has weight 0
+// beside a finite one of its wave (in the vector kernel the first score of a
+// lane must be finite, else the head is NaN).
 #include "attn_body.h"
 
 namespace fasttps {

@@ -24,9 +24,8 @@ constexpr uint64_t kLayerMagic = 0x4641535454505331ull;    // "FASTTPS1"
 constexpr uint64_t kWeightsMagic = 0x4641535454505357ull;  // "FASTTPSW"
 constexpr uint64_t kDeadMagic = 0xDEADDEADDEADDEADull;
 // attention blocks per step (256 CUs): 2 per CU (each lane with two tiles in
-// flight on the vector kernel); up
-// to four times as many, shorter splits when the batch's positions are ragged
-// (attention_plan).
+// flight on the vector kernel); up to four times as many, shorter splits when
+// the batch's positions are ragged (attention_plan).
 // Measured on MI355X: Phi-3 16-sequence ragged batch 101 -> 94 us and GQA
 // 4 x 32768 115 -> 103 us against 768 blocks throughout; then 512 blocks with
 // two tiles in flight against 768 with one: Phi-3 layer at KV 4096 61.7 ->
@@ -755,7 +754,7 @@ struct StepScratch {
   float* h1;
   float* a;
   int nsplit_cap;
-  bool noalloc;  // the vector path only, no test hooks, no timing events
+  bool noalloc;  // the vector projections only, no test hooks, no timing events
 };
 
 // Bytes of static scratch a step of `batch` sequences with nsplit splits
@@ -803,12 +802,16 @@ AttnPlan attention_plan(const fasttps_layer* l, const int32_t* pos, int32_t batc
     // Ragged batches on the vector kernel: two or four times the blocks, so that
     // the short sequences' splits do not end early, from 1024 and 2048 positions
     // a block up; below, the blocks' prologues and merges and the combine cost
-    // more (and on the matrix cores at any length). MI355X, layer step with 512 /
-    // 1024 / 2048 blocks: Phi-3, 4 sequences of 65-2500 entries (320 a block)
-    // 65.7 / 66.1 / 67.5 us, 3 of 500-8000 (800) 84.1 / 88.0 / 88.0, 16 of
-    // 65-2500 (1280) 101.0 / 101.6 / 108.2, 4 of 500-8000 (1060) 90.3 / 87.8 /
-    // 93.1, 16 of 500-8000 (4250) 186.8 / 185.8 / 184.7; matrix cores, d 128,
-    // groups of four, 4 of 500-8000 53.8 / 53.7 / 57.1
+    // more. MI355X, layer step with 512 / 1024 / 2048 blocks: Phi-3, 4 sequences
+    // of 65-2500 entries (320 a block) 65.7 / 66.1 / 67.5 us, 3 of 500-8000 (800)
+    // 84.1 / 88.0 / 88.0, 16 of 65-2500 (1280) 101.0 / 101.6 / 108.2, 4 of
+    // 500-8000 (1060) 90.3 / 87.8 / 93.1, 16 of 500-8000 (4250) 186.8 / 185.8 /
+    // 184.7. On the matrix cores one count for all: which is faster changes from
+    // batch to batch. 512 / 1024: d 128, groups of four, 4 of 500-8000 53.8 / 53.7
+    // (2048 57.1); groups of two, 32 of 256-8192 bf16 289.4 / 286.6, FP8 207.1 /
+    // 206.8, 4 of 500-16000 FP8 99.8 / 100.7; one head, FP8, Phi-3 3 of 30-30000
+    // 106.9 / 111.5, 4 of 500-16000 94.1 / 91.6, 16 of 512-4096 101.7 / 103.7, 32 of
+    // 256-8192 231.1 / 226.5
     const long per_block = total * c.n_kv_heads / kTargetAttnBlocks;
     const int ragged = minp == maxp || mfma || per_block < 1024 ? 1 : per_block < 2048 ? 2 : kRaggedAttnFactor;
     const long target = batch == 1 ? kTargetAttnBlocksOne : ragged * (long)kTargetAttnBlocks;
@@ -822,7 +825,12 @@ AttnPlan attention_plan(const fasttps_layer* l, const int32_t* pos, int32_t batc
     // 60.3 us, 20-400 ragged 65.5 / 59.6, 1000 70.8 / 69.0, 4000 118.1 / 120.4;
     // 512 pairs, 100-2000 ragged 100.1 / 94.5, FP8 79.1 / 77.0 (256 pairs: 67.8
     // / 70.4), 500-4096 ragged 128.4 / 129.2; Llama3-8B, 256 pairs, 20-400
-    // ragged 100.1 / 93.3, 512 pairs, 500-4096 ragged 214.7 / 220.6
+    // ragged 100.1 / 93.3, 512 pairs, 500-4096 ragged 214.7 / 220.6. At the limits:
+    // FP8 / INT8, Phi-3, 256 pairs, 1024 entries 64.7 / 64.5 against 62.4 / 62.5,
+    // 20-1024 ragged 64.7 / 64.6 against 61.8 / 62.3, 512 pairs, 2048 93.8 / 93.9
+    // both. Beyond 512 pairs the limit stays: 1024 pairs, 100-2048 ragged bf16
+    // 149.9 / 145.7, FP8 118.0 / 117.9; 2048 pairs, 512-4096 383.1 / 383.2, FP8 274.2 /
+    // 274.0 (1024 pairs 216.0 / 211.5, but groups of four, 512 pairs 252.0 / 261.0)
     const int pairs = batch * c.n_kv_heads;
     if (pairs >= kOneSplitPairs && maxn <= (pairs < 2 * kOneSplitPairs ? 1024 : 2048)) nsplit = 1;
     return AttnPlan{mfma, nsplit};

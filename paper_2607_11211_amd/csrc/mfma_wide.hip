@@ -1,12 +1,12 @@
 // Projections of large batches on the matrix cores (gfx950 MFMA): steps of
-// more than kWideMinBatch sequences.
+// kWideMinBatch to 64 sequences over layers of more than a few MB (wide_pays).
 //
 // The kernels of mfma_proj.hip give a grid row of blocks 16 sequences, so a
 // step of 64 streamed every weight four times. Here a block computes all
-// sequences of its rows and the weights are read once. What bounds it then is
-// the CU's load path: a block reads its weights (HBM) and the activation
-// operand of its k-tiles (L2), 4 bytes per input and sequence, which at 64
-// sequences is two to ten times its weights, at 80-100 GB/s per CU. So
+// sequences of its rows and the weights are read once. What a block loads is
+// then its weights (HBM) and the activation operand of its k-tiles (L2), 4 bytes
+// per input and sequence, which at 64 sequences is two to ten times its
+// weights; both wait in one queue. So
 //   * the loop runs over the k-tiles, and every operand tile meets all stripes
 //     of the block (up to NS at a time, their sums in registers) while it is
 //     in registers: the operand crosses the load path once per NS stripes;
@@ -34,8 +34,14 @@
 // MI355X, kernel us, the 16-sequence kernels -> these: Phi-3 at 64 sequences QKV
 // 49.0 -> 22.5, O 24.9 -> 10.2, gate/up 75.9 -> 29.9, down 43.6 -> 18.7 (layer
 // 468 -> 372); Llama3-8B at 32 sequences 29.9 -> 15.3, 16.3 -> 10.4, 88.0 ->
-// 43.2 (6.4 TB/s with the launch), 48.5 -> 25.7. Weights or operand pointed at
-// one tile (timing only): gate/up at 64 sequences 16 and 21 us of the 30.
+// 43.2, 48.5 -> 25.7. Gate/up at 64 sequences of Phi-3 (30 us, 1.2 MB a block, 40
+// GB/s per CU): with the weights pointed at one tile 16 us, with the operand at
+// one tile 21 (timing only), so the two streams' times add up for the most
+// part. By counters 302 MB go through L2 (63 % hits, 600 cycles a request on
+// average, about 10 KB in flight per CU), the matrix cores are busy 17 % and the
+// vector units 11 % of the cycles: it waits for loads, but neither for HBM (107 MB)
+// nor at the rate at which CUs read shared data alone (80-100 GB/s). Two or three
+// tiles in flight, rotated operand chunks and 32-bit offsets made no difference.
 #include "common.h"
 #include "kernels.h"
 
@@ -344,7 +350,9 @@ __global__ __launch_bounds__(256) void wide_pair_sum_kernel(const float* __restr
   dst[i] = split[b] ? src[i] + src[part + i] : src[i];
 }
 
-// stripes whose sums a lane holds at once
+// stripes whose sums a lane holds at once (6 beyond 32 sequences; with four
+// sequence tiles the compiler then spills 2 to 8 of the 256 registers, 12 to 36
+// bytes a lane: Phi-3's QKV at 64 sequences)
 constexpr int ns_max(int nbt) { return nbt <= 2 ? 8 : 6; }
 
 struct WideGeom {

@@ -233,7 +233,7 @@ class Layer:
 
     def step_noalloc(self, weights: Weights, x, pos, k_cache, v_cache, y, stream=None) -> None:
         """Enqueue one decode step that allocates nothing (the library's static
-        scratch array; vector-path kernels). Same contract as step."""
+        scratch array; the vector projections). Same contract as step."""
         pa, n = self._stage_pos(pos)
         _check(LIB.fasttps_decode_step_noalloc(self._h, weights.handle, _ptr(x), pa, n,
                                                _ptr(k_cache), _ptr(v_cache), _ptr(y), _stream_handle(stream)),
