@@ -886,18 +886,20 @@ int run_step(fasttps_layer* l, const fasttps_weights* w, const void* x, const in
   // hand-overs through coherent flags cost more than the separate kernels'
   // boundaries in a HIP graph (69.6 vs 54.4 us per Phi-3 layer at KV 4096).
   FusedShape fsh{};
-  fsh.head_dim = (int)d;
-  fsh.group = c.n_heads / c.n_kv_heads;
-  fsh.q = gemv_shape_b1((int)D, false);
-  fsh.o = gemv_shape_b1(c.n_heads * (int)d, false);
-  fsh.gu = gemv_shape_b1((int)D, true);
-  fsh.down = gemv_shape_b1(c.intermediate, false);
-  const bool fused_ok = batch == 1 && kvf == kKvBf16 && l->p_bf16 == 0 && nsplit <= fused_layer_max_splits() &&
-                        nsplit * c.n_kv_heads <= fused_layer_grid() && c.n_heads * (int)d <= 4096 &&
-                        fused_layer_supported(fsh);
   const bool fused = !mfma && !S.noalloc && !mlp_fused && l->gemm_path == FASTTPS_GEMM_FUSED;
-  if (fused && !fused_ok)
-    return fail(FASTTPS_ERR_UNSUPPORTED, "the fused kernel is built for one sequence of the Phi-3-mini layer shape");
+  if (fused) {
+    fsh.head_dim = (int)d;
+    fsh.group = c.n_heads / c.n_kv_heads;
+    fsh.q = gemv_shape_b1((int)D, false);
+    fsh.o = gemv_shape_b1(c.n_heads * (int)d, false);
+    fsh.gu = gemv_shape_b1((int)D, true);
+    fsh.down = gemv_shape_b1(c.intermediate, false);
+    const bool ok = batch == 1 && kvf == kKvBf16 && l->p_bf16 == 0 && nsplit <= fused_layer_max_splits() &&
+                    nsplit * c.n_kv_heads <= fused_layer_grid() && c.n_heads * (int)d <= 4096 &&
+                    fused_layer_supported(fsh);
+    if (!ok)
+      return fail(FASTTPS_ERR_UNSUPPORTED, "the fused kernel is built for one sequence of the Phi-3-mini layer shape");
+  }
 
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
