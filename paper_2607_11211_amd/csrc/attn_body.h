@@ -369,8 +369,9 @@ struct AttnBody {
   // for the test hooks, by the split that owns the new entry: whether this
   // sequence's q|k|v came in two parts, and q and k after RoPE
   __device__ __forceinline__ void write_dbg() {
-    if (a.qkv_split && own_new && g == 0 && tid == 0) a.qkv_split[b] = IO::kParts;
-    if (a.dbg_qk && own_new) {
+    if (!own_new) return;
+    if (a.qkv_split && g == 0 && tid == 0) a.qkv_split[b] = IO::kParts;
+    if (a.dbg_qk) {
       const int H = a.n_heads, Hkv = a.n_kv_heads;
       float* dq = a.dbg_qk + (size_t)b * (H + Hkv) * D;
       for (int i = tid; i < G * D; i += kThreads) dq[(size_t)g * G * D + i] = sm.q[i / D][i % D];
