@@ -55,6 +55,8 @@ BF16 = [
     _cfg("am_g2_d64_65", 137, 4, 2, 64, tuple(e for e in EDGES if e <= 128) + (65,)),
     _cfg("am_g2_d64_2p16", 138, 64, 32, 64, (1900, 148)),
     _cfg("am_g2_d64_2p16_1", 139, 64, 32, 64, (1900, 149)),
+    # one split of 8 tiles or more on the vector kernel: its tiles exchanged through LDS
+    _cfg("am_g2_d64_xch", 142, 32, 16, 64, (1000,) + tuple(9 * i for i in range(15))),
 ]
 
 

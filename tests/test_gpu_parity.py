@@ -33,10 +33,10 @@ SMALL = [
     # GQA group 4, d=128, long base, uneven MLP tile
     LayerConfig(name="s_gqa128", index=12, batch=3, hidden=1024, n_heads=8, n_kv_heads=2, head_dim=128,
                 intermediate=2824, rope_base=500000.0, max_seq=1100, pos=(5, 511, 1000)),
-    # one KV head, long context: 47 splits (past the one-wave combine's 32: the block combine)
+    # one KV head in a group of four, long context: 47 tiles of 64 positions, 24 splits on the matrix cores
     LayerConfig(name="s_kv1_47split", index=14, batch=1, hidden=256, n_heads=4, n_kv_heads=1, head_dim=64,
                 intermediate=688, rope_base=10000.0, max_seq=3136, pos=(3000,)),
-    # one KV head, longer context: 126 splits (the block combine, 16 groups of 8 splits at d = 64)
+    # longer context: 63 splits there (past the one-wave combine's 32: the block combine)
     LayerConfig(name="s_kv1_126split", index=15, batch=1, hidden=256, n_heads=4, n_kv_heads=1, head_dim=64,
                 intermediate=688, rope_base=10000.0, max_seq=8064, pos=(8001,)),
     # the smallest shapes the ABI takes: hidden 8 (one 16-byte chunk per row), MLP width 8, a
@@ -45,13 +45,32 @@ SMALL = [
                 intermediate=8, rope_base=10000.0, max_seq=1, pos=(0,)),
     LayerConfig(name="s_min_b3", index=17, batch=3, hidden=8, n_heads=2, n_kv_heads=1, head_dim=64,
                 intermediate=8, rope_base=10000.0, max_seq=2, pos=(0, 1, 1)),
-    # the two combine kernels at their boundary: 32 splits (one wave) and 33 (a block)
+    # the one-wave combine's two sizes at their boundary: 16 and 17 splits on the matrix cores
     LayerConfig(name="s_kv1_32split", index=23, batch=2, hidden=256, n_heads=4, n_kv_heads=1, head_dim=64,
                 intermediate=688, rope_base=10000.0, max_seq=2112, pos=(2048, 5)),
     LayerConfig(name="s_kv1_33split", index=24, batch=2, hidden=256, n_heads=4, n_kv_heads=1, head_dim=64,
                 intermediate=688, rope_base=10000.0, max_seq=2112, pos=(2049, 2048)),
-    # the block combine at d = 96 and d = 128 (10 and 8 thread groups per element): 79 splits over
-    # two KV heads, and 141 splits on one KV head with two query heads
+    # the two combine kernels at their boundary, 32 splits (one wave) and 33 (a block), on the vector
+    # kernel and on the matrix cores, and the one-wave combine's at 16 and 17 splits on the vector kernel
+    LayerConfig(name="s_one_32split", index=200, batch=2, hidden=256, n_heads=1, n_kv_heads=1, head_dim=64,
+                intermediate=688, rope_base=10000.0, max_seq=2112, pos=(2048, 5)),
+    LayerConfig(name="s_one_33split", index=201, batch=2, hidden=256, n_heads=1, n_kv_heads=1, head_dim=64,
+                intermediate=688, rope_base=10000.0, max_seq=2112, pos=(2049, 2048)),
+    LayerConfig(name="s_g4_32split", index=202, batch=2, hidden=256, n_heads=4, n_kv_heads=1, head_dim=64,
+                intermediate=688, rope_base=10000.0, max_seq=4224, pos=(4096, 5)),
+    LayerConfig(name="s_g4_33split", index=203, batch=2, hidden=256, n_heads=4, n_kv_heads=1, head_dim=64,
+                intermediate=688, rope_base=10000.0, max_seq=4224, pos=(4097, 4096)),
+    LayerConfig(name="s_one_16split", index=204, batch=2, hidden=256, n_heads=2, n_kv_heads=2, head_dim=96,
+                intermediate=688, rope_base=10000.0, max_seq=1100, pos=(1024, 5)),
+    LayerConfig(name="s_one_17split", index=205, batch=2, hidden=256, n_heads=2, n_kv_heads=2, head_dim=96,
+                intermediate=688, rope_base=10000.0, max_seq=1100, pos=(1025, 1024)),
+    # the block combine at d = 64 with 126 splits (16 groups of 8), at d = 96 and d = 128 (10 and 8
+    # thread groups per element) with 79 splits over two KV heads and 141 on one; and 71 splits on the
+    # matrix cores (one KV head with two query heads)
+    LayerConfig(name="s_one_126split", index=206, batch=1, hidden=256, n_heads=1, n_kv_heads=1, head_dim=64,
+                intermediate=688, rope_base=10000.0, max_seq=8064, pos=(8001,)),
+    LayerConfig(name="s_one_141split", index=207, batch=1, hidden=256, n_heads=1, n_kv_heads=1, head_dim=128,
+                intermediate=688, rope_base=500000.0, max_seq=9024, pos=(9000,)),
     LayerConfig(name="s_d96_79split", index=21, batch=1, hidden=256, n_heads=2, n_kv_heads=2, head_dim=96,
                 intermediate=688, rope_base=10000.0, max_seq=5056, pos=(5000,)),
     LayerConfig(name="s_d128_141split", index=22, batch=1, hidden=256, n_heads=2, n_kv_heads=1, head_dim=128,
@@ -76,9 +95,10 @@ SMALL = [
 ]
 
 
-# splits of 8 tiles and more with one or two query heads per KV head take the
+# splits of 8 tiles and more with one query head per KV head take the vector
 # attention's contiguous-load variant (whole-line loads, LDS exchange): every
-# head dimension and both group sizes, and a ragged batch
+# head dimension and a ragged batch; the same with groups of two, which run on
+# the matrix cores at these lengths
 XCH = [LayerConfig(name=f"x_d{d}_g{g}", index=70 + i, batch=1, hidden=512, n_heads=32 * g, n_kv_heads=32,
                    head_dim=d, intermediate=512, rope_base=10000.0, max_seq=8256, pos=(8192,))
        for i, (d, g) in enumerate([(64, 1), (96, 1), (128, 1), (64, 2), (96, 2), (128, 2)])]

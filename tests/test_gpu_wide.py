@@ -83,6 +83,7 @@ ATTENTION = [
     _long("w_g4_one", 153, 512, 64, 16, 128, 8000, _spread(17, 1, 1000)),
     # vector kernel: groups of two at d = 64
     _long("w_g2_d64_vec", 154, 512, 4, 2, 64, 8704, _spread(17, 100, 500)),
+    _long("w_g2_d64_vec_xch", 174, 512, 32, 16, 64, 8000, (1000,) + _spread(16, 0, 200)),
     # one head: tiles exchanged through LDS (8 or more per split), in two splits and in one
     _long("w_xch_d128", 155, 512, 16, 16, 128, 8000, _spread(17, 1060, 1100)),
     _long("w_xch_d96_one", 156, 512, 16, 16, 96, 8704, _spread(17, 600, 1000)),
